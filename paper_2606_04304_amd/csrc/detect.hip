@@ -520,7 +520,7 @@ constexpr int REG_LINE = 128 / (4 * REG_PX);  // workgroups that share a 128-byt
 template <int NR>
 __global__ __launch_bounds__(64 * REG_PX, 4) void detect_pixel_reg_kernel(const float *__restrict__ img, int n_chan, int n_pix,
                                                                 int mode, const float2 *__restrict__ stats,
-                                                                float thresh, float *__restrict__ snr_out,
+                                                                float thresh, float *__restrict__ pix_stats,
                                                                 nbsi_cand *__restrict__ cand, int cap,
                                                                 int *__restrict__ counter, unsigned *__restrict__ flags) {
     constexpr int CH = 1024;              // channels per staging round (16 registers)
@@ -530,7 +530,7 @@ __global__ __launch_bounds__(64 * REG_PX, 4) void detect_pixel_reg_kernel(const 
     __shared__ float tile[CH][REG_PX + 1];
     __shared__ float pool_all[REG_PX][64];
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    const int groups_per_row = (n_pix + REG_PX - 1) / REG_PX;
+    const int groups_per_row = n_pix / REG_PX;
     // XCD-aware order: workgroups are dealt to the 8 XCDs round robin, so the REG_LINE groups
     // that split each 128-byte line of a channel row go to blocks b, b + 8, ... of one XCD,
     // which run together and share the line in that XCD's L2
@@ -542,7 +542,6 @@ __global__ __launch_bounds__(64 * REG_PX, 4) void detect_pixel_reg_kernel(const 
     // staging: thread t loads pixels sp .. sp + 3 (16 bytes; n_pix is a multiple of 8) of
     // channels sc + CPS q
     const int sp = 4 * (t % TPC), sc = t / TPC;
-    const bool col_ok = gx0 + sp < n_pix;
     const float *src = img + (size_t)gy * n_pix + gx0 + sp;
     // the loads of round k + 1 are issued before round k's tile is read back, so they are in
     // flight across its barrier
@@ -550,7 +549,7 @@ __global__ __launch_bounds__(64 * REG_PX, 4) void detect_pixel_reg_kernel(const 
 #pragma unroll
         for (int q = 0; q < CH / CPS; q++) {
             const int c = k * CH + sc + CPS * q;
-            r[q] = (c < n_chan && col_ok) ? *reinterpret_cast<const float4 *>(src + (size_t)c * npix2)
+            r[q] = c < n_chan ? *reinterpret_cast<const float4 *>(src + (size_t)c * npix2)
                                           : make_float4(NAN, NAN, NAN, NAN);
         }
     };
@@ -588,17 +587,17 @@ __global__ __launch_bounds__(64 * REG_PX, 4) void detect_pixel_reg_kernel(const 
         for (int q = 0; q < CH / 64; q++) v[(CH / 64) * k + q] = tile[lane + 64 * q][wave];
     }
     const int x = gx0 + wave, y = gy;
-    if (x >= n_pix) return;  // no barriers below
+    // (n_pix is a multiple of REG_PX: every wave has a pixel, and all of them reach the barriers)
     // a spectrum holding a non-finite value is not searched (wave-uniform: one pixel per wave)
     const bool finite = ((s_bad >> wave) & 1u) == 0u;
     const bool in_hor = in_horizon(x, y, n_pix);
     if (in_hor && !finite && lane == 0 && flags) atomicOr(flags, NBSI_FLAG_CUBE_NONFINITE);
     const bool active = in_hor && finite;
     float *pool = pool_all[wave];
-    float scale = 1.f;
+    float scale = 1.f, med = 0.f;
     bool ok = active;
     if (active) {
-        const float med = reg_median<NR>(v, n_chan, pool, lane);
+        med = reg_median<NR>(v, n_chan, pool, lane);
         // the deviations x - med replace the values (rounded as the score rounds them); for the
         // MAD their magnitudes, with the signs kept in a bit mask, so that both selections rank
         // values held in registers (a rank over |x - med| computed on the fly has the compiler
@@ -626,7 +625,6 @@ __global__ __launch_bounds__(64 * REG_PX, 4) void detect_pixel_reg_kernel(const 
         const int c = lane + 64 * j;
         const float xv = v[j];  // x - med
         const float z = ok ? xv * inv : 0.f;
-        if (snr_out && c < n_chan) snr_out[(size_t)c * npix2 + (size_t)y * n_pix + x] = z;
         const bool hit = ok && c < n_chan && z >= thresh;
         // the neighbours are fetched (with every lane taking part) only when a lane crosses
         if (__ballot(hit) == 0ull) continue;
@@ -647,6 +645,49 @@ __global__ __launch_bounds__(64 * REG_PX, 4) void detect_pixel_reg_kernel(const 
             r.snr = z;
             cand[idx] = r;
         }
+    }
+    // the pixel's median and scale, for snr_cube_kernel (inv = 0: not searched)
+    if (pix_stats && lane == 0) {
+        pix_stats[(size_t)gy * n_pix + x] = ok ? med : 0.f;
+        pix_stats[npix2 + (size_t)gy * n_pix + x] = inv;
+    }
+}
+
+// The SNR cube from the medians and scales of detect_pixel_reg_kernel, which stand in the cube's
+// first two channel planes: channels c0 .. n_chan - 1, a thread takes 4 adjacent pixels of SNR_CPB
+// channels (all loads in flight) with 16-byte accesses.  Bound by HBM (8 bytes per voxel).  The
+// pixel kernel cannot write the cube well itself: it holds 4 pixels x all channels, and 16-byte
+// pieces of 128-byte lines leave its eight line-sharing workgroups at different times (4,096 x
+// 256^2, whole call: 3.25 ms with 4-byte stores from the lanes, 1.57 ms with 16-byte ones through
+// the tile, 1.22 ms with the two kernels, of which this one takes 0.36).
+constexpr int SNR_CPB = 8;
+__global__ __launch_bounds__(256) void snr_cube_kernel(const float *__restrict__ img, int n_chan, int n_pix, int mode,
+                                                       const float2 *__restrict__ stats, int c0, float *snr) {
+    const size_t npix2 = (size_t)n_pix * n_pix;
+    const size_t p = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (p >= npix2) return;
+    const int cb = c0 + blockIdx.y * SNR_CPB;
+    const float4 med = *reinterpret_cast<const float4 *>(snr + p);
+    const float4 inv = *reinterpret_cast<const float4 *>(snr + npix2 + p);
+    float4 x[SNR_CPB];
+#pragma unroll
+    for (int q = 0; q < SNR_CPB; q++)
+        if (cb + q < n_chan) x[q] = *reinterpret_cast<const float4 *>(img + (size_t)(cb + q) * npix2 + p);
+#pragma unroll
+    for (int q = 0; q < SNR_CPB; q++) {
+        const int c = cb + q;
+        if (c >= n_chan) break;
+        float e[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+        const float m[4] = {med.x, med.y, med.z, med.w}, s[4] = {inv.x, inv.y, inv.z, inv.w};
+        if (mode == NBSI_DETECT_PER_IMAGE) {  // the same standardised value the pixel kernel staged
+            const float2 st = stats[c];
+#pragma unroll
+            for (int i = 0; i < 4; i++) e[i] = st.y > 0.f ? (e[i] - st.x) / st.y : e[i] * 0.f;
+        }
+        // (a pixel that is not searched may hold non-finite values; + 0: no negative zeros)
+#pragma unroll
+        for (int i = 0; i < 4; i++) e[i] = s[i] != 0.f ? fmaf(e[i] - m[i], s[i], 0.f) : 0.f;
+        *reinterpret_cast<float4 *>(snr + (size_t)c * npix2 + p) = make_float4(e[0], e[1], e[2], e[3]);
     }
 }
 
@@ -953,10 +994,28 @@ hipError_t launch_detect_scan(const float *img, int n_chan, int n_pix, int mode,
                               float thresh, float *snr, nbsi_cand *cand, int cap, int *counter,
                               hipStream_t st, unsigned *flags) {
     const float2 *s2 = reinterpret_cast<const float2 *>(stats);
-    if (n_chan <= 64 * 64) {
-        const int n_blocks = n_pix * ((n_pix + REG_PX - 1) / REG_PX);
-        hipLaunchKernelGGL(detect_pixel_reg_kernel<64>, dim3(n_blocks), dim3(64 * REG_PX), 0, st, img, n_chan, n_pix,
-                           mode, s2, thresh, snr, cand, cap, counter, flags);
+    // (an SNR cube that overlaps the images takes the kernel that has read a pixel's spectrum
+    // whole before it writes that pixel's SNRs)
+    const size_t npix2 = (size_t)n_pix * n_pix, cube_bytes = sizeof(float) * npix2 * n_chan;
+    const uintptr_t a0 = (uintptr_t)img, b0 = (uintptr_t)snr;
+    const bool overlap = snr && a0 < b0 + cube_bytes && b0 < a0 + cube_bytes;
+    if (n_chan <= 64 * 64 && !overlap) {
+        // the spectrum's registers are sized to it: every selection pass visits all NR of them
+        const int n_blocks = n_pix * (n_pix / REG_PX);
+#define NBSI_REG(NR)                                                                                                 \
+    hipLaunchKernelGGL(detect_pixel_reg_kernel<NR>, dim3(n_blocks), dim3(64 * REG_PX), 0, st, img, n_chan, n_pix,    \
+                       mode, s2, thresh, snr, cand, cap, counter, flags)
+        if (n_chan <= 64 * 16) NBSI_REG(16);
+        else if (n_chan <= 64 * 32) NBSI_REG(32);
+        else NBSI_REG(64);
+#undef NBSI_REG
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess || !snr) return e;
+        // channels 2 and up, then the two planes that held the statistics
+        const unsigned nx = (unsigned)((npix2 / 4 + 255) / 256);
+        hipLaunchKernelGGL(snr_cube_kernel, dim3(nx, (unsigned)((n_chan - 2 + SNR_CPB - 1) / SNR_CPB)), dim3(256), 0,
+                           st, img, n_chan, n_pix, mode, s2, 2, snr);
+        hipLaunchKernelGGL(snr_cube_kernel, dim3(nx, 1), dim3(256), 0, st, img, 2, n_pix, mode, s2, 0, snr);
         return hipGetLastError();
     }
     const int ppw = detect_ppw(n_chan);

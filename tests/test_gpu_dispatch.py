@@ -1,0 +1,36 @@
+"""Edges of the size-dependent dispatches: shapes on both sides of every rule that picks a kernel
+or a register / tile count, against the oracle or against the general form."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2606_04304_amd as nb
+from test_gpu_parity import detect_parity
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("mode", [nb.NBSI_DETECT_PER_PIXEL, nb.NBSI_DETECT_PER_IMAGE])
+@pytest.mark.parametrize("n_chan,n_pix", [(12, 8), (1024, 8), (1025, 24), (2048, 16), (2049, 8), (4096, 8), (4097, 8)])
+def test_detect_register_counts(n_chan, n_pix, mode):
+    """Spectra at and just past 16, 32 and 64 registers of 64 channels, SNR cube included."""
+    detect_parity(n_chan, n_pix, mode)
+
+
+@pytest.mark.parametrize("mode", [nb.NBSI_DETECT_PER_PIXEL, nb.NBSI_DETECT_PER_IMAGE])
+@pytest.mark.parametrize("n_chan", [3, 10, 100, 1500])
+def test_detect_snr_cube_in_place(n_chan, mode):
+    """The SNR cube written over the images equals the one written beside them, and a pixel with
+    a non-finite value is zero in both."""
+    print(f"detect in place n_chan={n_chan} mode={mode}", flush=True)
+    rng = np.random.default_rng(n_chan)
+    cube = torch.from_numpy(rng.standard_normal((n_chan, 16, 16)).astype(np.float32)).to(DEV)
+    cube[n_chan // 2, 8, 9] = 30.0
+    cube[n_chan - 1, 7, 7] = float("nan")
+    rec, snr, n = nb.nbsi_detect(cube, mode=mode, want_snr=True)
+    both = cube.clone()
+    rec2, snr2, n2 = nb.nbsi_detect_noalloc(both, mode=mode, snr=both)
+    assert n == n2 and np.array_equal(rec, rec2)
+    assert torch.equal(snr, snr2)
+    assert torch.all(snr[:, 7, 7] == 0) and torch.isfinite(snr).all()
