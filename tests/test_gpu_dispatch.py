@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import paper_2606_04304_amd as nb
+from test_gpu_drift import test_dedoppler_matches_oracle as dedoppler_parity
 from test_gpu_parity import detect_parity
 
 pytestmark = pytest.mark.gpu
@@ -34,3 +35,11 @@ def test_detect_snr_cube_in_place(n_chan, mode):
     assert n == n2 and np.array_equal(rec, rec2)
     assert torch.equal(snr, snr2)
     assert torch.all(snr[:, 7, 7] == 0) and torch.isfinite(snr).all()
+
+
+@pytest.mark.parametrize("n_sub,n_chan,n_pix,max_drift", [(1, 3, 8, 16), (2, 33, 8, 16), (4, 35, 16, 16), (4, 67, 24, 16),
+                                                          (4, 68, 8, 15), (7, 130, 8, 16), (8, 65, 16, 16), (5, 64, 8, 0)])
+def test_dedoppler_segment_ends(n_sub, n_chan, n_pix, max_drift):
+    """Bands shorter than a segment, ending inside a step, and just past a segment's end; pixel
+    counts below a workgroup's; the full drift range and less."""
+    dedoppler_parity(n_sub, n_chan, n_pix, max_drift)
