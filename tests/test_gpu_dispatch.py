@@ -7,6 +7,7 @@ import torch
 import paper_2606_04304_amd as nb
 from test_gpu_drift import test_dedoppler_matches_oracle as dedoppler_parity
 from test_gpu_parity import detect_parity
+from test_gpu_search import _check_bank, _cube
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -43,3 +44,20 @@ def test_dedoppler_segment_ends(n_sub, n_chan, n_pix, max_drift):
     """Bands shorter than a segment, ending inside a step, and just past a segment's end; pixel
     counts below a workgroup's; the full drift range and less."""
     dedoppler_parity(n_sub, n_chan, n_pix, max_drift)
+
+
+@pytest.mark.parametrize("n_chan,n_pix", [(3, 8), (99, 8), (100, 16), (101, 8), (127, 8), (128, 24), (129, 8), (145, 8),
+                                          (256, 16), (257, 8), (383, 8), (640, 40)])
+def test_search_default_bank_edges(n_chan, n_pix):
+    """The default bank on bands shorter than its widths, at the ends of its 16-channel groups,
+    128-channel blocks and 64-channel segments: the cubes against the oracle, and the same records
+    with the width cube, from it, and from the widths found voxel by voxel."""
+    print(f"search default bank n_chan={n_chan} n_pix={n_pix}", flush=True)
+    lines = [(n_pix // 2, n_pix // 2, n_chan // 2, 1, 25.0)]
+    r = _cube(n_chan, n_pix, n_chan + n_pix, lines)
+    x = torch.from_numpy(r).to(DEV)
+    for q in (0.01, 0.4):  # few provisional detections, and nearly all voxels
+        rec, thr, k, S, W = nb.nbsi_search(x, fdr_q=q, want_cubes=True)
+        rec2, thr2, k2, _, _ = nb.nbsi_search(x, fdr_q=q)
+        assert (thr, k) == (thr2, k2) and np.array_equal(rec, rec2)
+        _check_bank(r, S, W)
