@@ -515,8 +515,10 @@ int image_plan_build(nbsi_ctx *ctx, const double *ant_xyz_host, int n_ant, const
                 if (fabs(dx) * nu_min / C_LIGHT > U * (1 + slack)) continue;
                 if (fabs(dy) * nu_min / C_LIGHT > U * (1 + slack)) continue;
                 const double v1 = dy * nu_min / C_LIGHT * 4.0 + M / 2, v2 = dy * nu_max / C_LIGHT * 4.0 + M / 2;
-                lo_row.push_back(std::max(0, (int)floor(std::min(v1, v2)) - 4));
-                hi_row.push_back(std::min(M - 1, (int)floor(std::max(v1, v2)) + 5));
+                // the footprint's rows at any frequency (1e-6 rows of slack against the kernel's
+                // own rounding; a row met only at the kernel's edge has weight zero)
+                lo_row.push_back(std::max(0, (int)floor(std::min(v1, v2) - 1e-6) - 3));
+                hi_row.push_back(std::min(M - 1, (int)floor(std::max(v1, v2) + 1e-6) + 4));
             }
             pairs.push_back(make_int2(a, b));
             dxy.push_back(make_double2(dx, dy));
@@ -561,6 +563,7 @@ int image_plan_build(nbsi_ctx *ctx, const double *ant_xyz_host, int n_ant, const
     p->n_pairs = (int)pairs.size();
 
     std::vector<int> band_off, band_items;
+    std::vector<int2> blk;
     std::vector<float> corr;
     if (method == NBSI_IMAGE_GRID) {
         // The image is the real part of the grid's transform, i.e. half the transform of the
@@ -585,6 +588,20 @@ int image_plan_build(nbsi_ctx *ctx, const double *ant_xyz_host, int n_ant, const
             // +-dx nu / (c du) + M/2 is then non-decreasing along the list for every channel
             auto key = [&](int it) { return (it & 1) ? -dxy[it >> 1].x : dxy[it >> 1].x; };
             std::stable_sort(bins[bnd].begin(), bins[bnd].end(), [&](int a, int b) { return key(a) < key(b); });
+            // the list entries that can reach each 16-column block: an item's first column is
+            // floor(+-dx nu / (c du) + M/2) - 3, non-decreasing along the list at every frequency
+            // (1e-6 columns of slack against the kernel's own rounding)
+            auto first_col = [&](int it, double nu) { return key(it) * nu / C_LIGHT * 4.0 + (double)(M / 2) - 3.0; };
+            const auto &bl = bins[bnd];
+            for (int b = 0, lo = 0, hi = 0; b < M / 16; b++) {
+                const double x0 = 16.0 * b - 7.0, x1 = 16.0 * b + 16.0;  // first columns of the block's items: [x0, x1)
+                while (lo < (int)bl.size() &&
+                       floor(std::max(first_col(bl[lo], nu_min), first_col(bl[lo], nu_max)) + 1e-6) < x0)
+                    lo++;
+                while (hi < (int)bl.size() && std::min(first_col(bl[hi], nu_min), first_col(bl[hi], nu_max)) - 1e-6 < x1)
+                    hi++;
+                blk.push_back(make_int2(lo, std::max(lo, hi)));
+            }
             band_items.insert(band_items.end(), bins[bnd].begin(), bins[bnd].end());
             band_off.push_back((int)band_items.size());
         }
@@ -619,6 +636,7 @@ int image_plan_build(nbsi_ctx *ctx, const double *ant_xyz_host, int n_ant, const
     if (ok && method == NBSI_IMAGE_GRID)
         ok = up((void **)&p->d_band_off, band_off.data(), sizeof(int) * band_off.size()) &&
              up((void **)&p->d_band_items, band_items.data(), sizeof(int) * band_items.size()) &&
+             up((void **)&p->d_blk, blk.data(), sizeof(int2) * blk.size()) &&
              up((void **)&p->d_corr, corr.data(), sizeof(float) * corr.size()) &&
              up((void **)&p->d_tmask, tmask.data(), sizeof(unsigned long long) * tmask.size()) &&
              up((void **)&p->d_tbase, tbase.data(), sizeof(int) * tbase.size()) &&
@@ -649,7 +667,7 @@ int nbsi_image_plan_destroy(nbsi_image_plan *p) {
     if (!p) return NBSI_EINVAL;
     DeviceGuard g(p->device);
     void *bufs[] = {p->d_xyz,      p->d_freq,       p->d_nb,   p->d_pairs, p->d_dxy,  p->d_band_off,
-                    p->d_band_items, p->d_corr, p->d_inb, p->d_tmask, p->d_tbase};
+                    p->d_band_items, p->d_blk,      p->d_corr, p->d_inb,   p->d_tmask, p->d_tbase};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     delete p;

@@ -293,6 +293,7 @@ int build_group_launches(nbsi_batch *b, const std::vector<int> &members, int gro
         j.dxy = p->d_dxy;
         j.band_off = p->d_band_off;
         j.band_items = p->d_band_items;
+        j.blk = p->d_blk;
         j.nb = p->d_nb;
         j.inb = p->d_inb;
         j.corr = p->d_corr;

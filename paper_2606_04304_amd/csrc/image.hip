@@ -414,12 +414,176 @@ __device__ __forceinline__ StageIn stage_load(int item, const float2 *__restrict
     return s;
 }
 
+// The row pass's gridding on the matrix cores (FP32 gridding of bands of at least 8 rows).  A block
+// of 8 grid rows x 16 grid columns gains, per baseline, the outer product of its row weights times V
+// and its column weights: with A[2 row + part][k] = wv_k[row] (Re, Im) V_k and B[k][col] = wu_k[col],
+// one v_mfma_f32_16x16x4_f32 adds the complex contributions of four baselines to the block, in
+// FP32.  A wave owns every fourth block of the band (all 8-row strips of it) in registers and walks
+// the plan's list range of each block, four entries at a step.  Staged per entry, transposed (entry
+// fastest, so that stores and the strided reads of a step are free of bank conflicts): the 2 R
+// values of A, the 8 column weights with a zero row below them, and the first footprint column; a
+// lane's column weight is row min(col - first column, 8) of that table, so entries that miss the
+// block (the ranges hold for every frequency of the plan) add zeros.
+// Bound by the matrix pipe (about 40 of its cycles per step, U + 1 steps per block and round) and by
+// the staging's LDS stores and kernel evaluations; the vector form below, where a thread owns 16
+// cells, reads 8 weights and forms 8 products per baseline and cell block and spends half of its
+// multiply-adds outside the footprints.  4,096 channels of 256^2, 8,046 pairs: the image call took
+// 3.30 ms with the vector form and 2.97 with this one; without this loop it takes 2.1 (transforms,
+// staging, column pass).  U = 2: the straight run covers two thirds of a block's entries; U = 3 and
+// 4 add zero products (3.00, 3.2 ms), four- and eight-byte wide reads of A need aligned starts and
+// lose as much again (3.07, 3.21), and products skipped one by one behind common reads are slower
+// (3.38).  Bands of four rows (512 x 512 images and up) half fill A: 1.71 against 1.47 ms for 300
+// channels of 512^2, so they keep the vector form, as the FP16 and BF16 modes do, which round every
+// weighted value.
+typedef float v4f __attribute__((ext_vector_type(4)));
+template <int N>
+struct IntC {
+    static constexpr int value = N;
+};
+
+template <int LOGM, int GE>
+struct MfmaShape {
+    using GS = GridShape<LOGM, GE>;
+    static constexpr bool OK = GS::R % 8 == 0;
+    static constexpr int STRIPS = OK ? GS::R / 8 : 1;        // 8-row strips of the band
+    static constexpr int BLOCKS = GS::M / 16;
+    static constexpr int BPW = BLOCKS / 4;                   // blocks per wave
+    static constexpr int PER = 2 * GS::R + 9 + 1;            // floats staged per entry
+    static constexpr int CAP0 = 2 * GS::BUF / PER;
+    // entries' stride: 4 x an odd number, so the 16 rows x 4 entries of a step fall in 64 banks
+    static constexpr int STR = (CAP0 / 4 % 2 ? CAP0 / 4 : CAP0 / 4 - 1) * 4;
+    static constexpr int U = 2;                              // steps that every block takes
+    // entries per round, one per thread; steps read up to 4 U entries past a round's end
+    static constexpr int CAP = STR - 4 * U < 256 ? STR - 4 * U : 256;
+    static_assert(!OK || (CAP >= 64 && STR * PER <= 2 * GS::BUF), "staging room");
+};
+
+template <int LOGM, int GE>
+__device__ __forceinline__ void grid_band_mfma(const float2 *__restrict__ cv_c, const double2 *__restrict__ dxy,
+                                               double sc, const int *__restrict__ items, int n_items,
+                                               const int2 *__restrict__ blk, const SetTest &bset, int row0, int c,
+                                               float2 *grid, float2 *tab) {
+    using GS = GridShape<LOGM, GE>;
+    using MS = MfmaShape<LOGM, GE>;
+    constexpr int M = GS::M, R = GS::R, STR = MS::STR, CAP = MS::CAP, BPW = MS::BPW, ST = MS::STRIPS;
+    float *s_a = reinterpret_cast<float *>(grid);  // [2 R][STR]
+    float *s_wu = s_a + 2 * R * STR;               // [9][STR]
+    int *s_gu = reinterpret_cast<int *>(s_wu + 9 * STR);
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int n_rounds = (n_items + CAP - 1) / CAP;
+    // round rr stages entries rr, rr + n_rounds, ...; thread t entry t n_rounds + rr
+    const int *my = items + t * n_rounds;
+    auto has = [&](int rr) { return rr < n_rounds && t * n_rounds + rr < n_items; };
+    int it_nxt = has(1) ? my[1] : 0;
+    StageIn cur;
+    if (has(0)) cur = stage_load(my[0], cv_c, dxy, bset, c);
+    // lanes 2 q, 2 q + 1: the ends of the list range of this wave's block q
+    int range = 0;
+    if (lane < 2 * BPW) {
+        const int2 v = blk[wave + 4 * (lane >> 1)];
+        range = (lane & 1) ? v.y : v.x;
+    }
+    fill_twiddles<LOGM>(tab, grid, t);  // (the band's LDS is free until staging)
+    v4f acc[BPW][ST];
+#pragma unroll
+    for (int q = 0; q < BPW; q++)
+#pragma unroll
+        for (int s = 0; s < ST; s++) acc[q][s] = v4f{0.f, 0.f, 0.f, 0.f};
+    const int k = lane >> 4, cl = lane & 15;
+    for (int rr = 0; rr < n_rounds; rr++) {
+        const int nk = (n_items - rr + n_rounds - 1) / n_rounds;
+        StageIn nxt;
+        if (has(rr + 1)) nxt = stage_load(it_nxt, cv_c, dxy, bset, c);
+        const int it_after = has(rr + 2) ? my[rr + 2] : 0;
+        __syncthreads();  // the previous round's staging area is free
+        for (int e = t; e < nk + 4 * MS::U; e += 256) {  // (entries past the round's end add zeros)
+            float2 val = make_float2(0.f, 0.f);
+            int gu0 = 1 << 20, gv0 = 0;
+            float ou = 0.f, ov = 0.f;
+            if (e < nk) {
+                const int kk = cur.item >> 1;
+                if ((cur.word >> (kk & 31)) & 1u) val = cur.val;
+                // mirrored item: conj V at -(u, v)
+                const double sgn = (cur.item & 1) ? -sc : sc;
+                if (cur.item & 1) val.y = -val.y;
+                const double cu = cur.d.x * sgn + (double)(M / 2), cvv = cur.d.y * sgn + (double)(M / 2);
+                const double fu = floor(cu), fv = floor(cvv);
+                gu0 = (int)fu - 3;
+                gv0 = (int)fv - 3;
+                ou = (float)(cu - fu);  // in [0, 1)
+                ov = (float)(cvv - fv);
+            }
+            s_gu[e] = gu0;
+            // cell offsets from the baseline's grid position, in cells: (j - 3) - o; the kernel is
+            // zero outside its support, rows j < 0 and j > 7 among it
+#pragma unroll
+            for (int j = 0; j < 8; j++) s_wu[j * STR + e] = es_kernel_fast(((float)(j - 3) - ou) * 0.25f);
+            s_wu[8 * STR + e] = 0.f;
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                const float wv = es_kernel_fast(((float)(row0 + r - gv0 - 3) - ov) * 0.25f);
+                s_a[(2 * r) * STR + e] = wv * val.x;
+                s_a[(2 * r + 1) * STR + e] = wv * val.y;
+            }
+        }
+        __syncthreads();
+        // staged entries of each range: list entries lo <= i n_rounds + rr < hi, rounded outwards
+        const int edge = max(0, range - rr);
+        const int bound = (lane & 1) ? (edge + n_rounds - 1) / n_rounds : edge / n_rounds;
+        const float *pa = s_a + cl * STR + k;
+        const float *pw = s_wu + k;
+        const int *pg = s_gu + k;
+        // steps of four entries from entry i on, for this wave's block q
+        auto steps = [&](auto n_steps, int q, int i) __attribute__((always_inline)) {
+            constexpr int U = decltype(n_steps)::value;
+            const int col = 16 * (wave + 4 * q) + cl;
+            int g[U];
+            float a[U][ST], b[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                g[u] = pg[i + 4 * u];
+#pragma unroll
+                for (int s = 0; s < ST; s++) a[u][s] = pa[16 * s * STR + i + 4 * u];
+            }
+#pragma unroll
+            for (int u = 0; u < U; u++) b[u] = pw[min((unsigned)(col - g[u]), 8u) * STR + i + 4 * u];
+#pragma unroll
+            for (int u = 0; u < U; u++)
+#pragma unroll
+                for (int s = 0; s < ST; s++)
+                    acc[q][s] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][s], b[u], acc[q][s], 0, 0, 0);
+        };
+        // the first U steps of every block in one straight run (a range that is shorter adds zeros),
+        // so that the reads of one block stand behind the products of another; the rest in loops
+#pragma unroll
+        for (int q = 0; q < BPW; q++) steps(IntC<MS::U>(), q, __builtin_amdgcn_readlane(bound, 2 * q));
+#pragma unroll
+        for (int q = 0; q < BPW; q++) {
+            const int i1 = __builtin_amdgcn_readlane(bound, 2 * q + 1);
+            for (int i = __builtin_amdgcn_readlane(bound, 2 * q) + 4 * MS::U; i < i1; i += 4) steps(IntC<1>(), q, i);
+        }
+        cur = nxt;
+        it_nxt = it_after;
+    }
+    __syncthreads();
+    // the lane holds rows 2 k and 2 k + 1 of each strip at its column, re and im adjacent
+#pragma unroll
+    for (int q = 0; q < BPW; q++)
+#pragma unroll
+        for (int s = 0; s < ST; s++) {
+            const int col = 16 * (wave + 4 * q) + cl, row = 8 * s + 2 * k;
+            grid[lds_at<M>(row, col)] = make_float2(acc[q][s][0], acc[q][s][1]);
+            grid[lds_at<M>(row + 1, col)] = make_float2(acc[q][s][2], acc[q][s][3]);
+        }
+    __syncthreads();
+}
+
 template <int LOGM, int PREC, int GE>
 __device__ __forceinline__ void grid_rows(const float2 *__restrict__ cvis, const double2 *__restrict__ dxy,
                                           const double *__restrict__ freq, const int *__restrict__ band_off,
-                                          const int *__restrict__ band_items, int n_pairs, const SetTest &bset,
-                                          float2 *__restrict__ inter, int band, int c, float2 *grid, float2 *tab,
-                                          float &vscale) {
+                                          const int *__restrict__ band_items, const int2 *__restrict__ blk, int n_pairs,
+                                          const SetTest &bset, float2 *__restrict__ inter, int band, int c, float2 *grid,
+                                          float2 *tab, float &vscale) {
     using GS = GridShape<LOGM, GE>;
     constexpr int M = GS::M, R = GS::R, RS = GS::RS, CPT = GS::CPT, COLT = GS::COLT, RPT = GS::RPT, CAP = GS::CAP;
     constexpr int n_pix = M / 2;
@@ -434,6 +598,11 @@ __device__ __forceinline__ void grid_rows(const float2 *__restrict__ cvis, const
     const float2 *cv_c = cvis + (size_t)c * n_pairs;
     const int k_begin = band_off[band], k_end = band_off[band + 1];
     const int n_items = k_end - k_begin;
+    constexpr bool MFMA = PREC == NBSI_PREC_FP32 && MfmaShape<LOGM, GE>::OK;
+    if constexpr (MFMA) {
+        grid_band_mfma<LOGM, GE>(cv_c, dxy, freq[c] / C_LIGHT * 4.0, band_items + k_begin, n_items,
+                                 blk + (size_t)band * MfmaShape<LOGM, GE>::BLOCKS, bset, row0, c, grid, tab);
+    } else {
     const int n_rounds = (n_items + CAP - 1) / CAP;
     // Round rr stages list entries rr, rr + n_rounds, ... (sorted by column and spread over the
     // whole band, so every wave has work in every round); thread t stages entry t n_rounds + rr,
@@ -563,6 +732,7 @@ __device__ __forceinline__ void grid_rows(const float2 *__restrict__ cvis, const
 #pragma unroll
         for (int r = 0; r < RPT; r++) grid[lds_at<M>(rown + r, col0 + q)] = acc[q][r];
     __syncthreads();
+    }
     fft_rows<LOGM, R, LOGM>(grid, tab, t);
     // keep image columns x: FFT index (x - n/2) mod M, times (-1)^(x - n/2); undo the FP16 scale;
     // the tile [x][R rows] is written as two rows per float4, contiguous over the workgroup
@@ -584,8 +754,9 @@ __device__ __forceinline__ void grid_rows(const float2 *__restrict__ cvis, const
 template <int LOGM, int PREC, int GE>
 __global__ __launch_bounds__(256) void grid_rows_kernel(const float2 *__restrict__ cvis, const double2 *__restrict__ dxy,
                                                         const double *__restrict__ freq, const int *__restrict__ band_off,
-                                                        const int *__restrict__ band_items, int n_pairs, int n_chan,
-                                                        SetTest bset, float2 *__restrict__ inter) {
+                                                        const int *__restrict__ band_items, const int2 *__restrict__ blk,
+                                                        int n_pairs, int n_chan, SetTest bset,
+                                                        float2 *__restrict__ inter) {
     using GS = GridShape<LOGM, GE>;
     __shared__ float2 grid[GS::BUF];
     __shared__ float2 tab[1 << (LOGM - 1)];
@@ -593,7 +764,7 @@ __global__ __launch_bounds__(256) void grid_rows_kernel(const float2 *__restrict
     const int id = blockIdx.x, xcd = id & 7, slot = id >> 3;
     const int c = ((slot / GS::NB) << 3) + xcd, band = slot % GS::NB;
     if (c >= n_chan) return;
-    grid_rows<LOGM, PREC, GE>(cvis, dxy, freq, band_off, band_items, n_pairs, bset, inter, band, c, grid, tab, vscale);
+    grid_rows<LOGM, PREC, GE>(cvis, dxy, freq, band_off, band_items, blk, n_pairs, bset, inter, band, c, grid, tab, vscale);
 }
 
 // Gridding of channel ranges of several sub-bands of one image size: task -> (job, channel,
@@ -612,7 +783,7 @@ __global__ __launch_bounds__(256) void grid_rows_batch_kernel(const ImgJob *__re
     const ImgJob &jb = jobs[j];
     const int local = task - jb.rows_task0;
     const SetTest bset{jb.inb, (jb.n_pairs + 31) >> 5};
-    grid_rows<LOGM, PREC, GE>(jb.cvis, jb.dxy, jb.freq, jb.band_off, jb.band_items, jb.n_pairs, bset, jb.inter,
+    grid_rows<LOGM, PREC, GE>(jb.cvis, jb.dxy, jb.freq, jb.band_off, jb.band_items, jb.blk, jb.n_pairs, bset, jb.inter,
                               local % GS::NB, local / GS::NB, grid, tab, vscale);
 }
 
@@ -778,7 +949,7 @@ static hipError_t launch_grid_m(const nbsi_image_plan *p, int precision, const f
     const dim3 gr((unsigned)(GridShape<LOGM, GE>::NB * c8));
 #define NBSI_ROWS(PR)                                                                                           \
     hipLaunchKernelGGL((grid_rows_kernel<LOGM, PR, GE>), gr, dim3(256), 0, st, cvis, p->d_dxy, p->d_freq,      \
-                       p->d_band_off, p->d_band_items, p->n_pairs, p->n_chan, bset, inter)
+                       p->d_band_off, p->d_band_items, p->d_blk, p->n_pairs, p->n_chan, bset, inter)
     if (precision == NBSI_PREC_FP16) NBSI_ROWS(NBSI_PREC_FP16);
     else if (precision == NBSI_PREC_BF16) NBSI_ROWS(NBSI_PREC_BF16);
     else NBSI_ROWS(NBSI_PREC_FP32);

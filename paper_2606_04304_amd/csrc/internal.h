@@ -65,6 +65,9 @@ struct nbsi_image_plan {
     int *d_band_off = nullptr;    // [n_bands + 1]
     int *d_band_items = nullptr;  // 2 * (index into d_pairs) + 1 if gridded at -(u, v) with conj V
     int n_band_items = 0;
+    // [n_bands][2 n_pix / 16]: entries [x, y) of a band's list hold every item whose footprint can
+    // reach grid columns 16 b .. 16 b + 15 at some frequency of the plan
+    int2 *d_blk = nullptr;
     float *d_corr = nullptr;      // [n_pix] 1 / (kernel Fourier transform) per image column
     // gridding plans: membership bitmap of B, [n_chan][(n_pairs + 31) / 32] words (bit k % 32 of
     // word k / 32 = pair k imaged at that channel), written by the count kernel
@@ -170,6 +173,7 @@ struct ImgJob {
     const int2 *pairs;
     const double2 *dxy;
     const int *band_off, *band_items, *nb;
+    const int2 *blk;
     const unsigned *inb;  // membership bitmap rows from the job's first channel
     const float *corr;
     float2 *cvis, *inter;

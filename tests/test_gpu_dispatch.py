@@ -4,9 +4,11 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2606_04304_amd as nb
+import synth
 from test_gpu_drift import test_dedoppler_matches_oracle as dedoppler_parity
-from test_gpu_parity import detect_parity
+from test_gpu_parity import _noise_vis, _rel, detect_parity
 from test_gpu_search import _check_bank, _cube
 
 pytestmark = pytest.mark.gpu
@@ -61,3 +63,31 @@ def test_search_default_bank_edges(n_chan, n_pix):
         rec2, thr2, k2, _, _ = nb.nbsi_search(x, fdr_q=q)
         assert (thr, k) == (thr2, k2) and np.array_equal(rec, rec2)
         _check_bank(r, S, W)
+
+
+@pytest.mark.parametrize("n_pix,n_ant,radius,freqs", [
+    (64, 3, 30.0, (70e6,)),                  # bands of a few entries, or none
+    (64, 60, 60.0, (40e6, 70e6, 110e6)),     # one octave and a half: block ranges far wider than a channel's
+    (128, 130, 120.0, (55e6, 85e6)),         # several staging rounds per band
+    (256, 352, 500.0, (69e6, 71e6)),
+    (256, 20, 60.0, (50e6, 100e6)),          # all baselines in the middle bands
+    (512, 40, 400.0, (60e6, 75e6)),          # four-row bands: the vector form
+])
+def test_image_grid_block_ranges(n_pix, n_ant, radius, freqs):
+    """Gridding over the plan's list ranges: plans whose frequencies move baselines by many grid
+    columns, sparse bands and bands of several rounds, against the direct-Fourier oracle."""
+    print(f"image grid ranges n_pix={n_pix} n_ant={n_ant}", flush=True)
+    xyz = synth.antenna_layout(n_ant, radius, 5 + n_pix)
+    freq = np.array(freqs)
+    plan = nb.nbsi_image_plan_create(xyz, freq, n_pix, nb.NBSI_IMAGE_GRID)
+    np.testing.assert_array_equal(plan.n_baselines(), oracle.count_baselines(xyz, freq, n_pix))
+    vis = _noise_vis(len(freqs), n_ant, n_pix + n_ant)
+    img = nb.nbsi_image(plan, torch.from_numpy(vis).to(DEV)).cpu().numpy()
+    if n_pix < 256:
+        ref = oracle.image_dft(vis, xyz, freq, n_pix, grid_n_pix=n_pix)
+    else:  # sampled pixels of the large images
+        rng = np.random.default_rng(n_pix)
+        pix = rng.integers(0, n_pix, (300, 2)).astype(np.int32)
+        ref = oracle.image_dft_pixels(vis, xyz, freq, n_pix, pix, grid_n_pix=n_pix)
+        img = img[:, pix[:, 1], pix[:, 0]]
+    assert _rel(img, ref)[0] < 1e-5
