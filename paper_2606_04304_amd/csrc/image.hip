@@ -806,6 +806,7 @@ struct ColShape {
     static constexpr int BUF = NX * RS;
     static constexpr int NXB = N / NX;                   // workgroups per channel
     static_assert(E >= 2 && E % 2 == 0 && RB >= 2, "float4 loads");
+    static_assert(E % (1 << FftPasses<LOGN>::log_radix(0)) == 0, "whole first-pass butterflies per thread");
 };
 
 template <int LOGM, int GE>
@@ -836,11 +837,14 @@ __device__ __forceinline__ void grid_cols(const float2 *__restrict__ inter, cons
         buf[lds_at<n>(xl, i + 1)] = make_float2(r[q].z, r[q].w);
     }
     __syncthreads();
+    // the fold and the transform's first pass (radix R0, no twiddles) in one: z[j], z[j + n / R0], ..
+    // of one butterfly are formed from the tile in registers
+    using FP = FftPasses<CS::LOGN>;
+    constexpr int R0 = 1 << FP::log_radix(0), PER_ROW = n / R0;
     float2 z[E];
 #pragma unroll
     for (int q = 0; q < E; q++) {
-        const int e = t + 256 * q;
-        const int xl = e / n, i = e % n;
+        const int g = t + 256 * (q / R0), xl = g / PER_ROW, i = g % PER_ROW + (q % R0) * PER_ROW;
         const float2 hi = buf[lds_at<n>(xl, i)];  // s[i + n]
         float2 lo = make_float2(0.f, 0.f);
         if (i) {
@@ -853,12 +857,14 @@ __device__ __forceinline__ void grid_cols(const float2 *__restrict__ inter, cons
     }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < E; q++) {
-        const int e = t + 256 * q;
-        buf[lds_at<n>(e / n, e % n)] = z[q];
+    for (int q = 0; q < E; q += R0) {
+        dft_r<R0>(z + q);
+        const int g = t + 256 * (q / R0), xl = g / PER_ROW, j = g % PER_ROW;
+#pragma unroll
+        for (int r = 0; r < R0; r++) buf[lds_at<n>(xl, j * R0 + r)] = z[q + r];
     }
     __syncthreads();
-    fft_rows<CS::LOGN, NX, LOGM>(buf, tab, t);
+    fft_rows<CS::LOGN, NX, LOGM, 1>(buf, tab, t);
     const int cnt = nb[c];
     const float inv = cnt > 0 ? (float)(0.5 / (double)cnt) : 0.f;
     bool bad = false;
