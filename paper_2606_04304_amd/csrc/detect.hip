@@ -56,12 +56,21 @@ __device__ __forceinline__ float wave_max_f(float v) {
     return v;
 }
 
-// Bin of x in [lo, hi] split into 256 equal parts: non-decreasing in x, safe for a zero-width
-// or denormal range (an infinite scale sends everything above lo to the last bin).
-__device__ __forceinline__ int value_bin(float x, float lo, float scale) {
-    const float t = (x - lo) * scale;
-    return t >= 256.f ? 255 : (t > 0.f ? (int)t : 0);
-}
+// Bin of x in [lo, hi] split into 256 equal parts: non-decreasing in x, safe for a zero-width range
+// (everything in bin 0) and, through the power of two h, for ranges so narrow that 256 over them
+// overflows (h = 2^100; lo is below 2^-76 then) or wider than the largest float (h = 1/2).
+struct BinMap {
+    float lo, h, scale;
+    __device__ __forceinline__ BinMap(float lo_, float hi) : lo(lo_) {
+        const float range = hi - lo;
+        h = range < 0x1p-100f ? 0x1p100f : range < INFINITY ? 1.f : 0.5f;
+        scale = 256.f / (hi * h - lo * h);
+    }
+    __device__ __forceinline__ int operator()(float x) const {
+        const float t = fmaf(x, h, -(lo * h)) * scale;
+        return t >= 256.f ? 255 : (t > 0.f ? (int)t : 0);
+    }
+};
 
 // Block-wide sum / min / max over SEL_NT threads through `red` (SEL_NT / 64 slots of LDS); every
 // thread gets the result.  Callers keep the calls uniform across the block.
@@ -91,6 +100,24 @@ __device__ __forceinline__ float block_min_f(float v, float *red) {
     for (int q = 0; q < SEL_NW; q++) s = fminf(s, red[q]);
     return s;
 }
+// Mean over the waves of a wave-uniform value, in wave order (waves with ok false take no part).
+__device__ __forceinline__ float block_mean_f(float v, bool ok, float *red, int *ired) {
+    const int w = threadIdx.x >> 6;
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+        red[w] = ok ? v : 0.f;
+        ired[w] = ok;
+    }
+    __syncthreads();
+    float s = 0.f;
+    int n = 0;
+#pragma unroll
+    for (int q = 0; q < SEL_NW; q++) {
+        s += red[q];
+        n += ired[q];
+    }
+    return s / (float)n;
+}
 __device__ __forceinline__ float block_max_f(float v, float *red) {
     v = wave_max_f(v);
     const int w = threadIdx.x >> 6;
@@ -111,127 +138,8 @@ struct SelLds {
     int ired[SEL_NW];
     float fred[SEL_NW];
     int sel[4];             // selected bin, values below it, values in it, pool fill
-    float res;              // the selected value
+    float res, res_next;    // the selected value and the next one up
 };
-
-// The rank-th smallest (0-based) of the values a block of SEL_NT threads enumerates (each(f)
-// calls f on every value the calling thread owns; exact order statistic).  Values are binned by value over the current range [lo, hi] into 256 LDS
-// counters; the bin index is a non-decreasing function of the value, so the bin holding the
-// rank-th value is found from the cumulative counts, and the range shrinks to that bin's own
-// min and max until at most SEL_POOL values remain, which are ranked directly.
-template <typename Each>
-__device__ __forceinline__ float block_kth(Each each, int rank, SelLds &L) {
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    float lo = INFINITY, hi = -INFINITY;
-    each([&](float x) __attribute__((always_inline)) {
-        lo = fminf(lo, x);
-        hi = fmaxf(hi, x);
-    });
-    lo = block_min_f(lo, L.fred);
-    hi = block_max_f(hi, L.fred);
-    int k = rank;
-    for (int iter = 0; iter < 40; iter++) {
-        if (!(hi > lo)) return lo;  // uniform: one value left in range
-        const float scale = 256.f / (hi - lo);
-        for (int e = t; e < 4 * 256; e += SEL_NT) (&L.hist[0][0])[e] = 0;
-        __syncthreads();
-        each([&](float x) __attribute__((always_inline)) {
-            if (x >= lo && x <= hi) atomicAdd(&L.hist[w & 3][value_bin(x, lo, scale)], 1u);
-        });
-        __syncthreads();
-        if (t < 256) L.cnt[t] = (int)(L.hist[0][t] + L.hist[1][t] + L.hist[2][t] + L.hist[3][t]);
-        __syncthreads();
-        // the bin holding rank k: threads 0..255 own one bin each (waves 0..3)
-        if (t < 256) {
-            const int cnt = L.cnt[t];
-            const int incl = wave_inclusive_scan(cnt, lane);
-            if (lane == 63) L.ired[w] = incl;
-            L.pool[t] = __int_as_float(cnt);  // park the count until the wave totals are known
-            L.pool[256 + t] = __int_as_float(incl);
-        }
-        __syncthreads();
-        if (t < 256) {
-            int base = 0;
-            for (int q = 0; q < w; q++) base += L.ired[q];
-            const int cnt = __float_as_int(L.pool[t]);
-            const int incl = base + __float_as_int(L.pool[256 + t]);
-            if (incl - cnt <= k && k < incl) {
-                L.sel[0] = t;
-                L.sel[1] = incl - cnt;
-                L.sel[2] = cnt;
-            }
-        }
-        if (t == 0) L.sel[3] = 0;
-        __syncthreads();
-        const int bsel = L.sel[0], below = L.sel[1], cnt_in = L.sel[2];
-        // min / max of the selected bin, and (when small) its values into the pool
-        float nlo = INFINITY, nhi = -INFINITY;
-        each([&](float x) __attribute__((always_inline)) {
-            if (x >= lo && x <= hi && value_bin(x, lo, scale) == bsel) {
-                nlo = fminf(nlo, x);
-                nhi = fmaxf(nhi, x);
-                if (cnt_in <= SEL_POOL) L.pool[atomicAdd(&L.sel[3], 1)] = x;
-            }
-        });
-        nlo = block_min_f(nlo, L.fred);  // (its barriers also order the pool writes)
-        nhi = block_max_f(nhi, L.fred);
-        k -= below;
-        if (cnt_in <= SEL_POOL) {
-            // exact rank within the pool: the pool value with k values below it (ties: any copy)
-            for (int e = t; e < cnt_in; e += SEL_NT) {
-                const float v = L.pool[e];
-                int less = 0, eq = 0;
-                for (int j = 0; j < cnt_in; j++) {
-                    const float y = L.pool[j];
-                    less += y < v;
-                    eq += y == v;
-                }
-                if (less <= k && k < less + eq) L.res = v;  // every writer writes the same value
-            }
-            __syncthreads();
-            const float r = L.res;
-            __syncthreads();
-            return r;
-        }
-        lo = nlo;
-        hi = nhi;
-    }
-    return lo;
-}
-
-// Median of the n_valid values the block enumerates (mean of the central pair for even
-// n_valid).
-template <typename Each>
-__device__ __forceinline__ float block_median(Each each, int n_valid, SelLds &L) {
-    const float vlo = block_kth(each, (n_valid - 1) / 2, L);
-    if (n_valid & 1) return vlo;
-    // rank n_valid/2: vlo itself when more than n_valid/2 values are <= vlo, else the next
-    // larger value
-    int le = 0;
-    float nxt = INFINITY;
-    each([&](float x) __attribute__((always_inline)) {
-        le += x <= vlo;
-        if (x > vlo) nxt = fminf(nxt, x);
-    });
-    le = block_sum(le, L.ired);
-    nxt = block_min_f(nxt, L.fred);
-    const float vhi = (le >= n_valid / 2 + 1) ? vlo : nxt;
-    return 0.5f * (vlo + vhi);
-}
-
-// A wave-uniform value moved to a scalar register (frees vector registers in the selection loops).
-__device__ __forceinline__ float uniform_f(float x) {
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
-}
-__device__ __forceinline__ int uniform_i(int x) { return __builtin_amdgcn_readfirstlane(x); }
-
-// The next float above / below a finite x (the bracket bounds around a dropped pivot value).
-__device__ __forceinline__ float float_up(float x) {
-    if (x == 0.f) return __int_as_float(1);  // smallest positive denormal
-    const int b = __float_as_int(x);
-    return __int_as_float(x > 0.f ? b + 1 : b - 1);
-}
-__device__ __forceinline__ float float_down(float x) { return -float_up(-x); }
 
 // Ascending bitonic sort of one value per lane across the wave (64 values).
 __device__ __forceinline__ float wave_sort64(float v, int lane) {
@@ -245,6 +153,164 @@ __device__ __forceinline__ float wave_sort64(float v, int lane) {
         }
     return v;
 }
+
+// The next float above / below a finite x (the bracket bounds around a dropped pivot value).
+__device__ __forceinline__ float float_up(float x) {
+    if (x == 0.f) return __int_as_float(1);  // smallest positive denormal
+    const int b = __float_as_int(x);
+    return __int_as_float(x > 0.f ? b + 1 : b - 1);
+}
+__device__ __forceinline__ float float_down(float x) { return -float_up(-x); }
+
+// The rank-th smallest (0-based) of the values a block of SEL_NT threads enumerates, and the next
+// one up when it was seen (have_hi): each(f) calls f on every value the calling thread owns, and on
+// NaN, which counts for nothing.  [a, b] is a proposal for the rank's place.  One pass counts the
+// values below a exactly and bins those inside [a, b], spread over 256 bins; the next gathers the
+// bin that holds the rank (ranked exactly by comparing all its values) or, when more than SEL_POOL
+// values share it, narrows [a, b] to its smallest and largest value.  A proposal that missed the
+// rank is replaced by the whole side the rank lies on, so the loop ends.
+template <typename Each>
+__device__ __forceinline__ float block_select(Each each, float a, float b, int rank, SelLds &L, float &vhi,
+                                              bool &have_hi) {
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    float vlo = a;
+    vhi = 0.f;
+    have_hi = false;
+    for (int iter = 0; iter < 64; iter++) {
+        const BinMap bin(a, b);
+        for (int e = t; e < 4 * 256; e += SEL_NT) (&L.hist[0][0])[e] = 0;
+        __syncthreads();
+        int below = 0;
+        each([&](float x) __attribute__((always_inline)) {
+            below += x < a;
+            if (x >= a && x <= b) atomicAdd(&L.hist[w & 3][bin(x)], 1u);
+        });
+        below = block_sum(below, L.ired);  // (its barriers also order the histogram)
+        const int k = rank - below;
+        // threads 0..255 own one bin each (waves 0..3)
+        int cnt = 0, incl = 0;
+        if (t < 256) {
+            cnt = (int)(L.hist[0][t] + L.hist[1][t] + L.hist[2][t] + L.hist[3][t]);
+            incl = wave_inclusive_scan(cnt, lane);
+        }
+        __syncthreads();
+        if (t < 256 && lane == 63) L.ired[w] = incl;
+        if (t == 0) {
+            L.sel[0] = -1;  // no bin holds the rank
+            L.sel[3] = 0;
+        }
+        __syncthreads();
+        if (t < 256) {
+            for (int q = 0; q < w; q++) incl += L.ired[q];
+            if (incl - cnt <= k && k < incl) {
+                L.sel[0] = t;
+                L.sel[1] = incl - cnt;
+                L.sel[2] = cnt;
+            }
+        }
+        __syncthreads();
+        const int bsel = L.sel[0], kb = k - L.sel[1], in_bin = L.sel[2];
+        const bool found = bsel >= 0, pool = found && in_bin <= SEL_POOL;
+        if (found && a == b) {  // in_bin values equal a
+            vlo = vhi = a;
+            have_hi = kb + 1 < in_bin;
+            break;
+        }
+        // the values of the bin, into the pool or as their smallest and largest; without a bin, the
+        // smallest and largest of all values
+        float nlo = INFINITY, nhi = -INFINITY;
+        each([&](float x) __attribute__((always_inline)) {
+            if (!found || (x >= a && x <= b && bin(x) == bsel)) {
+                if (pool) {
+                    L.pool[atomicAdd(&L.sel[3], 1)] = x;
+                } else {
+                    nlo = fminf(nlo, x);
+                    nhi = fmaxf(nhi, x);
+                }
+            }
+        });
+        if (pool) {
+            __syncthreads();
+            for (int e = t; e < in_bin; e += SEL_NT) {
+                const float v = L.pool[e];
+                int less = 0, eq = 0;
+                for (int j = 0; j < in_bin; j++) {
+                    const float y = L.pool[j];
+                    less += y < v;
+                    eq += y == v;
+                }
+                if (less <= kb && kb < less + eq) L.res = v;  // every writer writes the same value
+                if (less <= kb + 1 && kb + 1 < less + eq) L.res_next = v;
+            }
+            __syncthreads();
+            vlo = L.res;
+            vhi = L.res_next;
+            have_hi = kb + 1 < in_bin;
+            break;
+        }
+        nlo = block_min_f(nlo, L.fred);
+        nhi = block_max_f(nhi, L.fred);
+        if (found) {
+            a = nlo;
+            b = nhi;
+        } else if (k < 0) {  // below a
+            b = float_down(a);
+            a = nlo;
+        } else {
+            a = float_up(b);
+            b = nhi;
+        }
+        vlo = a;
+    }
+    __syncthreads();  // (the results have been read)
+    return vlo;
+}
+
+// Median of the n values of a block (mean of the central pair for even n; exact order statistics).
+// smp is one of the thread's values (NaN: none).  Every wave sorts its 64 samples and proposes the
+// ones a few places either side of the rank's expected place; their means over the waves bracket
+// the rank among about a tenth of the values.  compact(a, b, below) lists the values inside [a, b]
+// in LDS, per wave and without atomics, and counts those below a: one pass over all values, after
+// which the selection runs over the listed ones (list(f)).  It returns how many it listed, or -1
+// when it could not; then, or when the bracket missed the rank, the selection runs over all values.
+template <typename Each, typename Compact, typename List>
+__device__ __forceinline__ float block_median(Each each, Compact compact, List list, float smp, int n, SelLds &L) {
+    constexpr int D = 4;
+    const int lane = threadIdx.x & 63;
+    const int rank = (n - 1) / 2;
+    smp = smp == smp ? smp : INFINITY;
+    const float srt = wave_sort64(smp, lane);
+    const int s_n = __popcll(__ballot(smp < INFINITY));
+    const int p = (int)(((long long)rank * s_n) / n);
+    const float pa = __shfl(srt, max(p - D, 0), 64), pb = __shfl(srt, min(p + D, max(s_n - 1, 0)), 64);
+    const float a = block_mean_f(pa, s_n > 0, L.fred, L.ired);
+    const float b = block_mean_f(pb, s_n > 0, L.fred, L.ired);
+    int below = 0;
+    const int n_in = compact(a, b, below);
+    float vhi;
+    bool have_hi;
+    const float vlo = (rank >= below && rank < below + n_in) ? block_select(list, a, b, rank - below, L, vhi, have_hi)
+                                                             : block_select(each, a, b, rank, L, vhi, have_hi);
+    if (n & 1) return vlo;
+    if (have_hi) return 0.5f * (vlo + vhi);
+    // rank n / 2: vlo itself when more than n / 2 values are <= vlo, else the next larger value
+    int le = 0;
+    float nxt = INFINITY;
+    each([&](float x) __attribute__((always_inline)) {
+        le += x <= vlo;
+        nxt = fminf(nxt, x > vlo ? x : INFINITY);
+    });
+    le = block_sum(le, L.ired);
+    nxt = block_min_f(nxt, L.fred);
+    vhi = (le >= n / 2 + 1) ? vlo : nxt;
+    return 0.5f * (vlo + vhi);
+}
+
+// A wave-uniform value moved to a scalar register (frees vector registers in the selection loops).
+__device__ __forceinline__ float uniform_f(float x) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+__device__ __forceinline__ int uniform_i(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 // Pseudo-random 32-bit hash of (i, round), for reservoir sampling.
 __device__ __forceinline__ unsigned mix_hash(unsigned i, unsigned round) {
@@ -769,10 +835,13 @@ __global__ __launch_bounds__(64 * PPW) void detect_pixel_kernel(
 // threads per channel image.  Thread t owns column x = t % n_pix and the rows
 // y = y_lo(x) + t / n_pix, + G, ... (G = SEL_NT / n_pix row groups; for n_pix > SEL_NT a thread
 // owns several columns) inside the hemisphere, whose extent in each column is an integer square
-// root: coalesced row reads, no masking.  Up to 256 x 256 pixels a thread owns at most 64
-// values, which are read once and kept on chip (32 in registers, the rest in LDS), so every pass
-// of the selection runs from there; larger images are re-read each pass with eight loads in
-// flight (the passes of many channels at once do not fit the caches).
+// root: coalesced row reads, no masking.  Up to 256 x 256 pixels a thread owns at most 64 values,
+// which are read once and kept in registers, so every pass of the selections runs from there;
+// larger images are re-read each pass with eight loads in flight (the passes of many channels at
+// once do not fit the caches).  4,096 x 256^2: 1.16 ms, of which the loads, which nothing overlaps
+// (a workgroup's registers fill its CU), take about a third; 2.13 ms when half of the values stood
+// in LDS and each selection binned every value over the full range (the LDS adds of a bell-shaped
+// distribution collide in its middle bins), then found the bin's ends, then gathered it.
 __device__ __forceinline__ int isqrt_floor(int q) {  // largest r >= 0 with r * r <= q (q >= 0)
     int r = (int)sqrtf((float)q);
     while (r * r > q) r--;
@@ -780,14 +849,13 @@ __device__ __forceinline__ int isqrt_floor(int q) {  // largest r >= 0 with r * 
     return r;
 }
 
-constexpr int STATS_VR = 32;  // values per thread in registers (n_pix <= 256)
-constexpr int STATS_VL = 32;  // values per thread in LDS, [j][thread] (conflict-free rows)
-
-template <bool ONCHIP>
+// NV: values per thread in registers (0: read in each pass)
+constexpr int STATS_LIST = 1024;  // values a wave can list (a quarter of its 64 x 64)
+template <int NV>
 __global__ __launch_bounds__(SEL_NT) void image_stats_kernel(const float *__restrict__ img, int n_pix,
                                                              float2 *__restrict__ stats) {
     __shared__ SelLds L;
-    __shared__ float s_v[ONCHIP ? STATS_VL * SEL_NT : 1];
+    __shared__ float s_list[NV < 64 ? 1 : SEL_NW * STATS_LIST];
     const int c = blockIdx.x, t = threadIdx.x;
     const float *im = img + (size_t)c * n_pix * n_pix;
     const int h = n_pix / 2;
@@ -808,32 +876,32 @@ __global__ __launch_bounds__(SEL_NT) void image_stats_kernel(const float *__rest
         y0 = h - r + g;
         y1 = h + r;
     };
-    float v[ONCHIP ? STATS_VR : 1];
-    int nv = 0;
-    if constexpr (ONCHIP) {
-        // n_pix <= 256: one column, at most ceil(n_pix / G) <= 64 rows
+    // the thread's values, NaN where there is none (non-finite pixels take no part in the statistics)
+    float v[NV ? NV : 1];
+    float smp = NAN;  // one of them, from the middle of its column
+    if constexpr (NV > 0) {
         int y0 = 1, y1 = 0;
         if (on) rows(x0, y0, y1);
-        nv = y1 >= y0 ? (y1 - y0) / G + 1 : 0;
+        const int nv = y1 >= y0 ? (y1 - y0) / G + 1 : 0;  // at most ceil(n_pix / G) <= NV
 #pragma unroll
-        for (int j = 0; j < STATS_VR; j++) v[j] = j < nv ? im[(size_t)(y0 + j * G) * n_pix + x0] : 0.f;
+        for (int j = 0; j < NV; j++)  // (rows past the last read it again: no branch, all loads in flight)
+            v[j] = im[(nv ? y0 + min(j, nv - 1) * G : h) * n_pix + min(x0, n_pix - 1)];
 #pragma unroll
-        for (int j = 0; j < STATS_VL; j++) {
-            const int jj = STATS_VR + j;
-            s_v[j * SEL_NT + t] = jj < nv ? im[(size_t)(y0 + jj * G) * n_pix + x0] : 0.f;
+        for (int j = 0; j < NV; j++) {
+            v[j] = j < nv && __builtin_isfinite(v[j]) ? v[j] : NAN;
+            // (lane l samples around its own place, so that a wave's samples spread over the image)
+            smp = (j & 7) == (t & 7) && v[j] == v[j] && (j <= nv / 2 + 4 || smp != smp) ? v[j] : smp;
         }
-        // (the selection's first block reduction orders these LDS writes before any read)
+    } else if (on && x0 < n_pix) {
+        int y0, y1;
+        rows(x0, y0, y1);
+        if (y1 >= y0) smp = im[(size_t)((y0 + y1) / 2) * n_pix + x0];
+        smp = __builtin_isfinite(smp) ? smp : NAN;
     }
-    // every pass visits the finite values only (non-finite pixels take no part in the statistics)
     auto visit = [&](auto f) __attribute__((always_inline)) {
-        if constexpr (ONCHIP) {
+        if constexpr (NV > 0) {
 #pragma unroll
-            for (int j = 0; j < STATS_VR; j++)
-                if (j < nv && __builtin_isfinite(v[j])) f(v[j]);
-            for (int j = 0; j < nv - STATS_VR; j++) {
-                const float u = s_v[j * SEL_NT + t];
-                if (__builtin_isfinite(u)) f(u);
-            }
+            for (int j = 0; j < NV; j++) f(v[j]);
         } else {
             if (!on) return;
             for (int x = x0; x < n_pix; x += SEL_NT) {
@@ -856,18 +924,57 @@ __global__ __launch_bounds__(SEL_NT) void image_stats_kernel(const float *__rest
         }
     };
     int n_in = 0;
-    visit([&](float) __attribute__((always_inline)) { n_in++; });
+    visit([&](float x) __attribute__((always_inline)) { n_in += x == x; });
     n_in = block_sum(n_in, L.ired);
     if (n_in == 0) {  // no finite pixel in this channel image (uniform)
         if (t == 0) stats[c] = make_float2(0.f, 0.f);
         return;
     }
-    const float med = block_median([&](auto f) __attribute__((always_inline)) { visit(f); }, n_in, L);
-    const float mad = block_median(
-        [&](auto f) __attribute__((always_inline)) {
-            visit([&](float x) __attribute__((always_inline)) { f(fabsf(x - med)); });
-        },
-        n_in, L);
+    // the median, then the median of the deviations from it (which replace the values in registers)
+    float med = 0.f, mad = 0.f;
+#pragma unroll 1
+    for (int pass = 0; pass < 2; pass++) {
+        int listed = 0;  // by this wave
+        const float m = block_median(
+            [&](auto f) __attribute__((always_inline)) {
+                if constexpr (NV > 0) visit(f);
+                else visit([&](float x) __attribute__((always_inline)) { f(pass ? fabsf(x - med) : x); });
+            },
+            [&](float a, float b, int &below) __attribute__((always_inline)) {
+                if constexpr (NV < 64) return -1;  // (few values: the passes over them cost less than the list)
+                float *mine = s_list + (NV < 64 ? 0 : t >> 6) * STATS_LIST;
+                int lt = 0, n_list = 0;
+#pragma unroll
+                for (int j = 0; j < NV; j++) {
+                    const unsigned long long m_lt = __ballot(v[j] < a), m_in = __ballot(v[j] <= b) & ~m_lt;
+                    lt += __popcll(m_lt);
+                    const int at = n_list + __builtin_amdgcn_mbcnt_hi((unsigned)(m_in >> 32),
+                                                                      __builtin_amdgcn_mbcnt_lo((unsigned)m_in, 0u));
+                    if (((m_in >> (t & 63)) & 1ull) && at < STATS_LIST) mine[at] = v[j];
+                    n_list += __popcll(m_in);
+                }
+                listed = n_list;
+                // (counts per wave, added up by block_sum: one lane of each wave holds them)
+                below = block_sum((t & 63) == 0 ? lt : 0, L.ired);
+                const int full = block_sum((t & 63) == 0 && n_list > STATS_LIST, L.ired);
+                const int total = block_sum((t & 63) == 0 ? n_list : 0, L.ired);
+                return full ? -1 : total;
+            },
+            [&](auto f) __attribute__((always_inline)) {
+                for (int i = t & 63; i < listed; i += 64) f(s_list[NV < 64 ? 0 : (t >> 6) * STATS_LIST + i]);
+            },
+            smp, n_in, L);
+        if (pass == 0) {
+            med = m;
+            smp = fabsf(smp - med);
+            if constexpr (NV > 0) {
+#pragma unroll
+                for (int j = 0; j < NV; j++) v[j] = fabsf(v[j] - med);
+            }
+        } else {
+            mad = m;
+        }
+    }
     if (t == 0) stats[c] = make_float2(med, MAD_K * mad);
 }
 
@@ -981,12 +1088,13 @@ int detect_ppw(int n_chan) {
 hipError_t launch_detect_stats(const float *img, int n_chan, int n_pix, int mode, float *stats,
                                hipStream_t st) {
     if (mode != NBSI_DETECT_PER_IMAGE) return hipSuccess;
-    if (n_pix <= 256)
-        hipLaunchKernelGGL(image_stats_kernel<true>, dim3(n_chan), dim3(SEL_NT), 0, st, img, n_pix,
-                           reinterpret_cast<float2 *>(stats));
-    else
-        hipLaunchKernelGGL(image_stats_kernel<false>, dim3(n_chan), dim3(SEL_NT), 0, st, img, n_pix,
-                           reinterpret_cast<float2 *>(stats));
+    // values per thread: ceil(n_pix / G) rows of a column, G = SEL_NT / n_pix row groups
+#define NBSI_STATS(NV) \
+    hipLaunchKernelGGL(image_stats_kernel<NV>, dim3(n_chan), dim3(SEL_NT), 0, st, img, n_pix, reinterpret_cast<float2 *>(stats))
+    if (n_pix <= 128) NBSI_STATS(16);
+    else if (n_pix <= 256) NBSI_STATS(64);
+    else NBSI_STATS(0);
+#undef NBSI_STATS
     return hipGetLastError();
 }
 

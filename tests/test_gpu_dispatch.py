@@ -91,3 +91,41 @@ def test_image_grid_block_ranges(n_pix, n_ant, radius, freqs):
         ref = oracle.image_dft_pixels(vis, xyz, freq, n_pix, pix, grid_n_pix=n_pix)
         img = img[:, pix[:, 1], pix[:, 0]]
     assert _rel(img, ref)[0] < 1e-5
+
+
+@pytest.mark.parametrize("n_pix", [8, 64, 128, 136, 256, 264])
+def test_image_statistics_register_counts(n_pix):
+    """Per-image medians and MADs where a thread holds 1 to 64 values and where it holds none, on
+    noise, few distinct values, one value, ramps that mislead the samples, a range wider than the
+    largest float, subnormal values, outliers and non-finite pixels."""
+    print(f"image statistics n_pix={n_pix}", flush=True)
+    rng = np.random.default_rng(n_pix)
+    cube = rng.standard_normal((12, n_pix, n_pix)).astype(np.float32)
+    cube[1] = rng.integers(-2, 3, (n_pix, n_pix))
+    cube[2] = 7.5
+    cube[3] = np.arange(n_pix * n_pix, dtype=np.float32).reshape(n_pix, n_pix)
+    cube[4] = -cube[3].T
+    cube[5] *= 1e38
+    cube[6] *= 1e-41
+    cube[7, ::3, ::2] = 1e30
+    cube[8, rng.random((n_pix, n_pix)) < 0.4] = np.nan
+    cube[9, ::2] = np.inf
+    cube[10] = np.exp(8.0 * cube[10])
+    x = torch.from_numpy(cube).to(DEV)
+    beam = torch.full((12, 3), float("nan"), dtype=torch.float64, device=DEV)
+    cands = torch.tensor([[n_pix // 2, n_pix // 2, c, 1, 0] for c in range(12)], dtype=torch.int32, device=DEV)
+    # Stage II reports the channel's 1.4826 MAD through chi2_red = rss / (sigma^2 (n - 7))
+    fit = nb.fits_host(nb.nbsi_stage2(x, cands, beam, half=2), 12)
+    h = n_pix // 2
+    yy, xx = np.mgrid[:n_pix, :n_pix]
+    hor = (xx - h) ** 2 + (yy - h) ** 2 < h * h
+    for c in range(12):
+        v = cube[c][hor]
+        v = v[np.isfinite(v)]
+        med = np.float32(0.5) * (np.sort(v)[(v.size - 1) // 2] + np.sort(v)[v.size // 2])
+        d = np.sort(np.abs(v - med))
+        mad = np.float32(0.5) * (d[(v.size - 1) // 2] + d[v.size // 2])
+        sigma = float(np.float32(1.482602218505602) * mad)
+        if np.isfinite(fit["chi2_red"][c]) and fit["rss"][c] > 0 and sigma > 0:
+            got = np.sqrt(fit["rss"][c] / (fit["chi2_red"][c] * (25 - 7)))
+            assert abs(got - sigma) <= 1e-6 * sigma, (c, got, sigma)
