@@ -74,64 +74,120 @@ __global__ __launch_bounds__(256) void stamps_kernel(const float *__restrict__ c
     out[e] = (_Float16)fminf(fmaxf(v, -65504.f), 65504.f);
 }
 
-// ---------------- forward ----------------
-// One wave per 32 x 32 tile of (row, output channel); four waves per workgroup stack along rows.
-template <int CIN, int CINP, int COUT, bool IN_STAMP, bool OUT_F32>
-__global__ __launch_bounds__(256) void conv_fwd_kernel(const _Float16 *__restrict__ in, const int *__restrict__ index,
-                                                       int n_stamps, int n, const _Float16 *__restrict__ w16,
-                                                       const float *__restrict__ bias, void *__restrict__ out) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int M = n * NPOS;
-    const int m0 = (blockIdx.x * 4 + wave) * 32;
-    if (m0 >= M) return;  // uniform per wave; the kernel has no barriers
-    const int co0 = blockIdx.y * 32;
-    const int i = lane & 31, kq = (lane >> 5) * 8;
-    const int m = m0 + i;
-    const bool mv = m < M;
-    const int b = mv ? m / NPOS : 0, p = mv ? m % NPOS : 0;
-    const int y = p / SP, x = p % SP;
-    const _Float16 *src = nullptr;
-    bool sv = mv;
+// ---------------- convolutions (forward, and the data gradient) ----------------
+// Both are the same product: out[m][j] = sum over (tap, channel) of in[row m shifted by tap][channel]
+// w[j][tap][channel].  A workgroup takes 128 consecutive rows (a 32-row tile per wave) and stages the
+// stamps they belong to in LDS, position-major with 16 bytes of padding per position (an odd number
+// of 16-byte chunks, so the b128 reads of 32 positions are spread over the banks) and one position
+// of zeros for the taps that leave the stamp.  A wave multiplies each staged fragment with the
+// weights of all 32-column tiles, which come from the caches in fragment order; the sum runs over
+// taps, then channels, in order.  Bound by the staging and the latency of the weight reads: screening
+// 4,096 stamps, the three forward layers take 47, 36 and 32 us; 48, 57 and 101 when each lane gathered
+// its rows from memory once per tap and read its weights a cache line per output.  (Two tiles per
+// wave and whole stamps per workgroup were both slower: 53, 37, 41 and 59, 83, 72 us.)
+template <int C>
+struct ConvLds {
+    static constexpr int PITCH = C + 8;  // halves per staged position
+    static constexpr int stamps(int rows) { return (rows + NPOS - 2) / NPOS + 1; }  // that `rows` rows can touch
+    static constexpr int halves(int rows) { return (stamps(rows) * NPOS + 1) * PITCH; }
+    static_assert((PITCH / 8) % 2 == 1, "odd 16-byte chunks per position");
+};
+
+// Stages stamps b0 .. b0 + n_b - 1 (those below n) as [position][C] and the zero position after
+// them; from stamps [33][81] through index, or from activations [b][81][C].
+template <int CIN, int C, bool IN_STAMP>
+__device__ __forceinline__ void stage_stamps(const _Float16 *__restrict__ in, const int *__restrict__ index,
+                                             int n_stamps, int n, int b0, int n_b, _Float16 *lds) {
+    constexpr int PITCH = ConvLds<C>::PITCH;
+    const int t = threadIdx.x;
     if constexpr (IN_STAMP) {
-        const int s = index ? index[b] : b;
-        sv = mv && s >= 0 && s < n_stamps;
-        src = in + (size_t)(sv ? s : 0) * SC * NPOS;
-    } else {
-        src = in + (size_t)b * NPOS * CINP;
-    }
-    const _Float16 *wrow = w16 + (size_t)(co0 + i) * 9 * CINP;
-    v16f acc;
+        for (int l = 0; l < n_b; l++) {
+            const int b = b0 + l;
+            const int si = b < n ? (index ? index[b] : b) : -1;
+            const bool ok = si >= 0 && si < n_stamps;  // (uniform)
+            const _Float16 *src = in + (size_t)(ok ? si : 0) * SC * NPOS;
+            _Float16 *dst = lds + l * NPOS * PITCH;
+            // eight channels of a position at a time: coalesced reads along the positions, one write
+            // (padded channels are zero: their weights are, and the products must be)
+#pragma unroll 2
+            for (int e = t; e < C / 8 * NPOS; e += 256) {
+                const int c8 = e / NPOS * 8, p = e % NPOS;
+                v8h v = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-    for (int r = 0; r < 16; r++) acc[r] = 0.f;
-    for (int tap = 0; tap < 9; tap++) {
-        const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
-        const bool ok = sv && yy >= 0 && yy < SP && xx >= 0 && xx < SP;
-        const int pp = ok ? yy * SP + xx : 0;
-#pragma unroll
-        for (int c0 = 0; c0 < CINP; c0 += 16) {
-            const int ci = c0 + kq;
-            v8h a = {0, 0, 0, 0, 0, 0, 0, 0};
-            if (ok) {
-                if constexpr (IN_STAMP) {
-#pragma unroll
-                    for (int e = 0; e < 8; e++) a[e] = (ci + e < CIN) ? src[(ci + e) * NPOS + pp] : (_Float16)0;
-                } else {
-                    a = *reinterpret_cast<const v8h *>(src + pp * CINP + ci);
-                }
+                for (int q = 0; q < 8; q++)
+                    if (ok && c8 + q < CIN) v[q] = src[(c8 + q) * NPOS + p];
+                *reinterpret_cast<v8h *>(dst + p * PITCH + c8) = v;
             }
-            const v8h w = *reinterpret_cast<const v8h *>(wrow + tap * CINP + ci);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, w, acc, 0, 0, 0);
+        }
+    } else {
+        constexpr int CH = C / 8;  // 16-byte chunks per position
+        const int rows = min(n_b, n - b0) * NPOS;
+        const v8h *src = reinterpret_cast<const v8h *>(in + (size_t)b0 * NPOS * C);
+#pragma unroll 4
+        for (int e = t; e < rows * CH; e += 256)
+            *reinterpret_cast<v8h *>(lds + (e / CH) * PITCH + (e % CH) * 8) = src[e];
+    }
+    for (int e = t; e < PITCH; e += 256) lds[n_b * NPOS * PITCH + e] = (_Float16)0;
+}
+
+// acc[j] = the products of this wave's 32 rows from m0 on with column tile j.  SIGN: +1 reads
+// position + tap offset (forward), -1 position - tap offset (data gradient).
+template <int C, int JT, int SIGN>
+__device__ __forceinline__ void conv_tiles(const _Float16 *lds, int n_b, int b0, int m0, int M,
+                                           const _Float16 *__restrict__ w, int lane, v16f (&acc)[JT]) {
+    constexpr int PITCH = ConvLds<C>::PITCH;
+    const int kq = (lane >> 5) * 8, m = m0 + (lane & 31);
+    const bool mv = m < M;
+    const int base = mv ? (m / NPOS - b0) * NPOS : 0, p = m % NPOS, y = p / SP, x = p % SP;
+#pragma unroll
+    for (int j = 0; j < JT; j++)
+#pragma unroll
+        for (int q = 0; q < 16; q++) acc[j][q] = 0.f;
+    const v8h *wf = reinterpret_cast<const v8h *>(w) + lane;  // fragment f of the weights: wf[64 f]
+#pragma unroll
+    for (int tap = 0; tap < 9; tap++) {
+        const int yy = y + SIGN * (tap / 3 - 1), xx = x + SIGN * (tap % 3 - 1);
+        const bool ok = mv && yy >= 0 && yy < SP && xx >= 0 && xx < SP;
+        const _Float16 *src = lds + (ok ? base + yy * SP + xx : n_b * NPOS) * PITCH + kq;
+#pragma unroll
+        for (int c0 = 0; c0 < C; c0 += 16) {
+            const v8h a = *reinterpret_cast<const v8h *>(src + c0);
+#pragma unroll
+            for (int j = 0; j < JT; j++)
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, wf[64 * ((tap * (C / 16) + c0 / 16) * JT + j)], acc[j],
+                                                                0, 0, 0);
         }
     }
-    const int co = co0 + i;
-    const float bc = bias[co];
+}
+
+template <int CIN, int CINP, int COUT, bool IN_STAMP, bool OUT_F32>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void conv_fwd_kernel(const _Float16 *__restrict__ in, const int *__restrict__ index,
+                                                       int n_stamps, int n, const _Float16 *__restrict__ w16,
+                                                       const float *__restrict__ bias, void *__restrict__ out) {
+    constexpr int ROWS = 128, JT = COUT / 32;
+    __shared__ __attribute__((aligned(16))) _Float16 lds[ConvLds<CINP>::halves(ROWS)];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int M = n * NPOS;
+    const int w0 = blockIdx.x * ROWS, b0 = w0 / NPOS;
+    const int n_b = min((min(w0 + ROWS, M) - 1) / NPOS + 1, n) - b0;
+    stage_stamps<CIN, CINP, IN_STAMP>(in, index, n_stamps, n, b0, n_b, lds);
+    __syncthreads();
+    const int m0 = w0 + wave * 32;
+    if (m0 >= M) return;  // (no barriers below)
+    v16f acc[JT];
+    conv_tiles<CINP, JT, 1>(lds, n_b, b0, m0, M, w16, lane, acc);
 #pragma unroll
-    for (int r = 0; r < 16; r++) {
-        const int mm = m0 + acc_row(r, lane);
-        if (mm >= M) continue;
-        const float z = fmaxf(acc[r] + bc, 0.f);
-        if constexpr (OUT_F32) reinterpret_cast<float *>(out)[(size_t)mm * COUT + co] = z;
-        else reinterpret_cast<_Float16 *>(out)[(size_t)mm * COUT + co] = (_Float16)z;
+    for (int j = 0; j < JT; j++) {
+        const int co = 32 * j + (lane & 31);
+        const float bc = bias[co];
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+            const int mm = m0 + acc_row(r, lane);
+            if (mm >= M) continue;
+            const float z = fmaxf(acc[j][r] + bc, 0.f);
+            if constexpr (OUT_F32) reinterpret_cast<float *>(out)[(size_t)mm * COUT + co] = z;
+            else reinterpret_cast<_Float16 *>(out)[(size_t)mm * COUT + co] = (_Float16)z;
+        }
     }
 }
 
@@ -364,46 +420,34 @@ __global__ __launch_bounds__(256) void bgrad_final_kernel(const float *__restric
 // dA[m][ci] = [A_prev[m][ci] > 0] sum_{tap, co} dZ[m (-) tap][co] W[co][ci][tap],
 // with W read transposed as WT[ci][tap][co].  Also the largest |dA| (as an ordered integer).
 template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void dgrad_kernel(const _Float16 *__restrict__ dZ, const _Float16 *__restrict__ wt,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void dgrad_kernel(const _Float16 *__restrict__ dZ, const _Float16 *__restrict__ wt,
                                                     const _Float16 *__restrict__ a_prev, int n, float *__restrict__ dA,
                                                     unsigned *__restrict__ maxbits) {
+    constexpr int ROWS = 128, JT = CIN / 32;
+    __shared__ __attribute__((aligned(16))) _Float16 lds[ConvLds<COUT>::halves(ROWS)];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int M = n * NPOS;
-    const int m0 = (blockIdx.x * 4 + wave) * 32;
-    if (m0 >= M) return;  // uniform per wave; no barriers
-    const int ci0 = blockIdx.y * 32;
-    const int i = lane & 31, kq = (lane >> 5) * 8;
-    const int m = m0 + i;
-    const bool mv = m < M;
-    const int b = mv ? m / NPOS : 0, p = mv ? m % NPOS : 0;
-    const int y = p / SP, x = p % SP;
-    const _Float16 *wrow = wt + (size_t)(ci0 + i) * 9 * COUT;
-    v16f acc;
-#pragma unroll
-    for (int r = 0; r < 16; r++) acc[r] = 0.f;
-    for (int tap = 0; tap < 9; tap++) {
-        // Z[q] met this position through tap (dy, dx) when q = (y - dy + 1, x - dx + 1)
-        const int qy = y - (tap / 3 - 1), qx = x - (tap % 3 - 1);
-        const bool ok = mv && qy >= 0 && qy < SP && qx >= 0 && qx < SP;
-        const _Float16 *zrow = dZ + ((size_t)b * NPOS + (ok ? qy * SP + qx : 0)) * COUT;
-#pragma unroll
-        for (int c0 = 0; c0 < COUT; c0 += 16) {
-            const int cc = c0 + kq;
-            v8h a = {0, 0, 0, 0, 0, 0, 0, 0};
-            if (ok) a = *reinterpret_cast<const v8h *>(zrow + cc);
-            const v8h w = *reinterpret_cast<const v8h *>(wrow + tap * COUT + cc);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, w, acc, 0, 0, 0);
-        }
-    }
-    const int c = ci0 + i;
+    const int w0 = blockIdx.x * ROWS, b0 = w0 / NPOS;
+    const int n_b = min((min(w0 + ROWS, M) - 1) / NPOS + 1, n) - b0;
+    stage_stamps<COUT, COUT, false>(dZ, nullptr, 0, n, b0, n_b, lds);
+    __syncthreads();
+    const int m0 = w0 + wave * 32;
+    if (m0 >= M) return;  // (no barriers below)
+    v16f acc[JT];
+    // Z[q] met this position through tap (dy, dx) when q = (y - dy + 1, x - dx + 1)
+    conv_tiles<COUT, JT, -1>(lds, n_b, b0, m0, M, wt, lane, acc);
     float mx = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; r++) {
-        const int mm = m0 + acc_row(r, lane);
-        if (mm >= M) continue;
-        const float v = (float)a_prev[(size_t)mm * CIN + c] > 0.f ? acc[r] : 0.f;
-        dA[(size_t)mm * CIN + c] = v;
-        mx = fmaxf(mx, fabsf(v));
+    for (int j = 0; j < JT; j++) {
+        const int c = 32 * j + (lane & 31);
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+            const int mm = m0 + acc_row(r, lane);
+            if (mm >= M) continue;
+            const float v = (float)a_prev[(size_t)mm * CIN + c] > 0.f ? acc[j][r] : 0.f;
+            dA[(size_t)mm * CIN + c] = v;
+            mx = fmaxf(mx, fabsf(v));
+        }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
@@ -426,17 +470,26 @@ __global__ void fill_u32_kernel(unsigned *p, int n, unsigned v) {
     if (e < n) p[e] = v;
 }
 
-// FP16 copies of the convolution weights: W16[co][tap][ci (padded)] and WT16[ci][tap][co].
+// Index of weight (output j of J, tap, input channel k of K) in fragment order: the 64 x 8 halves that
+// one matrix instruction takes (32 outputs, 16 input channels of one tap) are contiguous, so a
+// wave's load of them touches eight cache lines instead of one per output.
+__device__ __forceinline__ int frag_index(int j, int J, int tap, int k, int K) {
+    const int f = (tap * (K / 16) + k / 16) * (J / 32) + j / 32, lane = j % 32 + 32 * (k % 16 / 8);
+    return (f * 64 + lane) * 8 + k % 8;
+}
+
+// FP16 copies of the convolution weights in fragment order: outputs co over padded inputs ci (the
+// forward pass), and outputs ci over inputs co (the data gradient).
 __global__ __launch_bounds__(256) void pack_weights_kernel(const float *__restrict__ w, int cout, int cin, int cinp,
                                                            _Float16 *__restrict__ w16, _Float16 *__restrict__ wt16) {
     const int e = blockIdx.x * 256 + threadIdx.x;
     if (e < cout * 9 * cinp) {
         const int co = e / (9 * cinp), rem = e % (9 * cinp), tap = rem / cinp, ci = rem % cinp;
-        w16[e] = ci < cin ? (_Float16)w[(co * cin + ci) * 9 + tap] : (_Float16)0;
+        w16[frag_index(co, cout, tap, ci, cinp)] = ci < cin ? (_Float16)w[(co * cin + ci) * 9 + tap] : (_Float16)0;
     }
     if (wt16 && e < cin * 9 * cout) {
         const int ci = e / (9 * cout), rem = e % (9 * cout), tap = rem / cout, co = rem % cout;
-        wt16[e] = (_Float16)w[(co * cin + ci) * 9 + tap];
+        wt16[frag_index(ci, cin, tap, co, cout)] = (_Float16)w[(co * cin + ci) * 9 + tap];
     }
 }
 
@@ -509,7 +562,7 @@ hipError_t pack_weights(nbsi_net *net, hipStream_t st) {
         const int cin = dims[l][0], cinp = dims[l][1], cout = dims[l][2];
         const long n = std::max((long)cout * 9 * cinp, (long)cin * 9 * cout);
         hipLaunchKernelGGL(pack_weights_kernel, dim3(blocks(n)), dim3(256), 0, st, net->theta + offs[l], cout, cin,
-                           cinp, net->w16[l], net->wt16[l]);
+                           cinp, net->w16[l], l ? net->wt16[l] : nullptr);
     }
     net->packed = true;
     return hipGetLastError();
@@ -530,11 +583,11 @@ hipError_t forward(nbsi_net *net, const uint16_t *stamps, int n_stamps, const in
     const _Float16 *x = reinterpret_cast<const _Float16 *>(stamps);
     const int M = n * NPOS;
     const dim3 blk(256);
-    hipLaunchKernelGGL((conv_fwd_kernel<33, 48, 32, true, false>), dim3(blocks(M, 128), 1), blk, 0, st, x, index,
+    hipLaunchKernelGGL((conv_fwd_kernel<33, 48, 32, true, false>), dim3(blocks(M, 128)), blk, 0, st, x, index,
                        n_stamps, n, net->w16[0], net->theta + OFF_B1, (void *)net->a1);
-    hipLaunchKernelGGL((conv_fwd_kernel<32, 32, 64, false, false>), dim3(blocks(M, 128), 2), blk, 0, st,
+    hipLaunchKernelGGL((conv_fwd_kernel<32, 32, 64, false, false>), dim3(blocks(M, 128)), blk, 0, st,
                        (const _Float16 *)net->a1, nullptr, 0, n, net->w16[1], net->theta + OFF_B2, (void *)net->a2);
-    hipLaunchKernelGGL((conv_fwd_kernel<64, 64, 32, false, true>), dim3(blocks(M, 128), 1), blk, 0, st,
+    hipLaunchKernelGGL((conv_fwd_kernel<64, 64, 32, false, true>), dim3(blocks(M, 128)), blk, 0, st,
                        (const _Float16 *)net->a2, nullptr, 0, n, net->w16[2], net->theta + OFF_B3, (void *)net->a3);
     hipLaunchKernelGGL(head_kernel, dim3(blocks(n, 8)), blk, 0, st, net->a3, n, net->theta, labels, index, n_stamps,
                        net->feat, logits, net->dz, net->lossb);
@@ -575,13 +628,13 @@ hipError_t backward(nbsi_net *net, const uint16_t *stamps, int n_stamps, const i
                        net->dZ);
     // layer 3 (input a2, 64 -> 32)
     weight_grads<64, 64, 32, false>(net, net->a2, nullptr, 0, n, 3, OFF_W3, OFF_B3, grad, st);
-    hipLaunchKernelGGL((dgrad_kernel<64, 32>), dim3(blocks(M, 128), 2), blk, 0, st, (const _Float16 *)net->dZ,
+    hipLaunchKernelGGL((dgrad_kernel<64, 32>), dim3(blocks(M, 128)), blk, 0, st, (const _Float16 *)net->dZ,
                        (const _Float16 *)net->wt16[2], (const _Float16 *)net->a2, n, net->dA, net->maxbits);
     hipLaunchKernelGGL(dz_convert_kernel, dim3(blocks((long)M * 64)), blk, 0, st, net->dA, (long)M * 64, net->maxbits,
                        net->scale, 3, 2, net->dZ);
     // layer 2 (input a1, 32 -> 64)
     weight_grads<32, 32, 64, false>(net, net->a1, nullptr, 0, n, 2, OFF_W2, OFF_B2, grad, st);
-    hipLaunchKernelGGL((dgrad_kernel<32, 64>), dim3(blocks(M, 128), 1), blk, 0, st, (const _Float16 *)net->dZ,
+    hipLaunchKernelGGL((dgrad_kernel<32, 64>), dim3(blocks(M, 128)), blk, 0, st, (const _Float16 *)net->dZ,
                        (const _Float16 *)net->wt16[1], (const _Float16 *)net->a1, n, net->dA, net->maxbits + 1);
     hipLaunchKernelGGL(dz_convert_kernel, dim3(blocks((long)M * 32)), blk, 0, st, net->dA, (long)M * 32,
                        net->maxbits + 1, net->scale, 2, 1, net->dZ);
@@ -649,7 +702,6 @@ int nbsi_net_create(nbsi_ctx *ctx, const float *params_host, int max_batch, nbsi
     rc = rc ? rc : net_alloc(net, (size_t)32 * 9 * 48, &net->w16[0]);
     rc = rc ? rc : net_alloc(net, (size_t)64 * 9 * 32, &net->w16[1]);
     rc = rc ? rc : net_alloc(net, (size_t)32 * 9 * 64, &net->w16[2]);
-    rc = rc ? rc : net_alloc(net, (size_t)33 * 9 * 32, &net->wt16[0]);
     rc = rc ? rc : net_alloc(net, (size_t)32 * 9 * 64, &net->wt16[1]);
     rc = rc ? rc : net_alloc(net, (size_t)64 * 9 * 32, &net->wt16[2]);
     if (rc) {

@@ -8,6 +8,8 @@ import oracle
 import paper_2606_04304_amd as nb
 import synth
 from test_gpu_drift import test_dedoppler_matches_oracle as dedoppler_parity
+from test_gpu_net import _stamps
+from test_gpu_net import test_forward_matches_oracle as forward_parity
 from test_gpu_parity import _noise_vis, _rel, detect_parity
 from test_gpu_search import _check_bank, _cube
 
@@ -129,3 +131,19 @@ def test_image_statistics_register_counts(n_pix):
         if np.isfinite(fit["chi2_red"][c]) and fit["rss"][c] > 0 and sigma > 0:
             got = np.sqrt(fit["rss"][c] / (fit["chi2_red"][c] * (25 - 7)))
             assert abs(got - sigma) <= 1e-6 * sigma, (c, got, sigma)
+
+
+@pytest.mark.parametrize("n", [2, 5, 8, 19, 128, 511])
+def test_net_row_groups(n):
+    """Batches whose 128-row groups start and end at every place of a stamp, a last group of one
+    row (n = 19) and of whole groups only (n = 128): against the oracle, and every logit bit for bit
+    that of the stamp in another place of a batch (each output is one sum in a fixed order)."""
+    forward_parity(n, 50 + n)
+    net = nb.Net(synth.net_init(50 + n), max_batch=512)
+    x = torch.from_numpy(_stamps(n, 50 + n)).to(DEV)
+    z = net.forward(x)
+    for shift in (1, n // 2, n - 1):
+        order = ((torch.arange(n) + shift) % n).to(torch.int32).to(DEV)
+        assert torch.equal(net.forward(x, index=order), z[order.long()])
+    assert torch.equal(net.forward(x[n - 1:].contiguous()), z[n - 1:])
+    net.close()
