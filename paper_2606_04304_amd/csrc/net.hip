@@ -223,17 +223,21 @@ __global__ __launch_bounds__(256) void head_kernel(const float *__restrict__ a3,
     }
 }
 
-// One workgroup: dL/dw4, dL/db4, the mean loss, and the first gradient scale.
-__global__ __launch_bounds__(256) void head_reduce_kernel(const float *__restrict__ feat, const float *__restrict__ dz,
-                                                          const float *__restrict__ lossb, int n,
-                                                          const float *__restrict__ theta, float *__restrict__ grad,
-                                                          float *__restrict__ loss, float *__restrict__ scale) {
-    __shared__ float r_w[8][32], r_d[8], r_l[8], r_m[8];
+// One workgroup: dL/dw4, dL/db4, the mean loss, and the first gradient scale; clears the maxima of
+// the two data gradients.  Bound by the latency of its rounds of loads (32 rows a round: 18 us at
+// batch 512 with 8).
+constexpr int HR_NT = 1024, HR_G = HR_NT / 32;
+__global__ __launch_bounds__(HR_NT) void head_reduce_kernel(const float *__restrict__ feat, const float *__restrict__ dz,
+                                                            const float *__restrict__ lossb, int n,
+                                                            const float *__restrict__ theta, float *__restrict__ grad,
+                                                            float *__restrict__ loss, float *__restrict__ scale,
+                                                            unsigned *__restrict__ maxbits) {
+    __shared__ float r_w[HR_G][32], r_d[HR_G], r_l[HR_G], r_m[HR_G];
     const int t = threadIdx.x, c = t & 31, j = t >> 5;
     float sw = 0.f, sd = 0.f, sl = 0.f, mx = 0.f;
     // (unrolled so that the loads are issued ahead of the in-order sums)
 #pragma unroll 8
-    for (int b = j; b < n; b += 8) {
+    for (int b = j; b < n; b += HR_G) {
         const float d = dz[b];
         sw += d * feat[b * 32 + c];
         if (c == 0) {
@@ -248,15 +252,16 @@ __global__ __launch_bounds__(256) void head_reduce_kernel(const float *__restric
         r_l[j] = sl;
         r_m[j] = mx;
     }
+    if (t < 2) maxbits[t] = 0u;
     __syncthreads();
     if (t < 32) {
         float s = 0.f;
-        for (int q = 0; q < 8; q++) s += r_w[q][t];
+        for (int q = 0; q < HR_G; q++) s += r_w[q][t];
         grad[OFF_W4 + t] = s;
     }
     if (t == 0) {
         float d = 0.f, l = 0.f, m = 0.f, mw = 0.f;
-        for (int q = 0; q < 8; q++) {
+        for (int q = 0; q < HR_G; q++) {
             d += r_d[q];
             l += r_l[q];
             m = fmaxf(m, r_m[q]);
@@ -280,11 +285,68 @@ __global__ __launch_bounds__(256) void dz3_kernel(const float *__restrict__ a3, 
     dZ[e] = a3[e] > 0.f ? (_Float16)(v * scale[3]) : (_Float16)0;
 }
 
+// Bias gradient, first level: part q of the rows, [q rows, (q + 1) rows), summed.  A thread reads 8
+// channels of a row with one 16-byte load; the row lanes of each channel are summed in a fixed
+// order, so the result is deterministic.
+template <int COUT>
+__device__ __forceinline__ void bgrad_partial(const _Float16 *__restrict__ dZ, int M, int rows, int q,
+                                              float *__restrict__ partial) {
+    constexpr int CG = COUT / 8, RL = 256 / CG;  // 8-channel groups per row, row lanes
+    static_assert(COUT % 8 == 0 && 256 % CG == 0, "whole 16-byte groups");
+    __shared__ float red[RL][COUT + 1];
+    const int t = threadIdx.x, g = t % CG, rl = t / CG;
+    const int m0 = q * rows, m1 = min(M, m0 + rows);
+    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int m = m0 + rl; m < m1; m += RL) {
+        const v8h x = *reinterpret_cast<const v8h *>(dZ + (size_t)m * COUT + 8 * g);
+#pragma unroll
+        for (int i = 0; i < 8; i++) s[i] += (float)x[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; i++) red[rl][8 * g + i] = s[i];
+    __syncthreads();
+    if (t < COUT) {
+        float a = 0.f;
+        for (int r = 0; r < RL; r++) a += red[r][t];
+        partial[(size_t)q * COUT + t] = a;
+    }
+}
+
+// Bias gradient, second level: each channel's partials over RL lanes, the lanes in a fixed
+// order, the gradient scale undone.
+template <int COUT>
+__device__ __forceinline__ void bgrad_final(const float *__restrict__ partial, int n_part, float scale,
+                                            float *__restrict__ grad) {
+    constexpr int RL = 256 / COUT;
+    __shared__ float red[256];
+    const int t = threadIdx.x, co = t % COUT, rl = t / COUT;
+    float s = 0.f;
+#pragma unroll 8
+    for (int q = rl; q < n_part; q += RL) s += partial[(size_t)q * COUT + co];
+    red[t] = s;
+    __syncthreads();
+    if (t < COUT) {
+        float a = 0.f;
+#pragma unroll
+        for (int r = 0; r < RL; r++) a += red[r * COUT + t];
+        grad[t] = a / scale;
+    }
+}
+
 // Weight gradient partials: D[co][k] = sum over this split's rows m of dZ[m][co] X[m (+) tap][ci].
+// The rows of workgroups after the last split form the bias gradient's first level: n_part parts of
+// `rows` rows (a launch of its own cost about 4 us per layer).
 template <int CIN, int CINP, int COUT, bool IN_STAMP>
 __global__ __launch_bounds__(256) void wgrad_kernel(const _Float16 *__restrict__ dZ, const _Float16 *__restrict__ in,
-                                                    const int *__restrict__ index, int n_stamps, int n, int chunk,
-                                                    float *__restrict__ partial) {
+                                                    const int *__restrict__ index, int n_stamps, int n, int ksplit,
+                                                    int chunk, float *__restrict__ partial, int n_part, int rows,
+                                                    float *__restrict__ bias_partial) {
+    if ((int)blockIdx.y >= ksplit) {
+        const int q = (blockIdx.y - ksplit) * gridDim.x + blockIdx.x;
+        if (q < n_part) bgrad_partial<COUT>(dZ, n * NPOS, rows, q, bias_partial);
+        return;
+    }
     constexpr int K = 9 * CINP;
     constexpr int KT = (K + 31) / 32;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -342,10 +404,18 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const _Float16 *__restrict__
 // Sum the partials, undo the gradient scale, write the oracle layout [o][i][dy][dx].  A
 // workgroup takes 64 consecutive (co, k) of the partials' own layout (contiguous reads); its
 // four waves sum the splits q = w, w + 4, ... and are then added in wave order, so the result
-// is deterministic.  Padded input channels (ci >= cin) are skipped.
-__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restrict__ partial, int ksplit, int cout,
-                                                           int cin, int cinp, const float *__restrict__ scale, int slot,
-                                                           float *__restrict__ grad, int off) {
+// is deterministic.  Padded input channels (ci >= cin) are skipped.  The last workgroup forms the
+// bias gradient from its partials.
+template <int COUT>
+__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restrict__ partial, int ksplit, int cin,
+                                                           int cinp, const float *__restrict__ scale, int slot,
+                                                           float *__restrict__ grad, int off, int off_b,
+                                                           const float *__restrict__ bias_partial, int n_part) {
+    if (blockIdx.x + 1 == gridDim.x) {
+        bgrad_final<COUT>(bias_partial, n_part, scale[slot], grad + off_b);
+        return;
+    }
+    constexpr int cout = COUT;
     __shared__ float red[4][64];
     const int K = 9 * cinp;
     const int t = threadIdx.x, l = t & 63, w = t >> 6;
@@ -364,56 +434,6 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float *__restri
     if (ci >= cin) return;
     const float a = ((red[0][l] + red[1][l]) + red[2][l]) + red[3][l];
     grad[off + (co * cin + ci) * 9 + tap] = a / scale[slot];
-}
-
-// Bias gradient, first level: workgroup q sums dZ over its rows [q rows, (q + 1) rows).  A
-// thread reads 8 channels of a row with one 16-byte load; the row lanes of each channel are
-// summed in a fixed order, so the result is deterministic.
-template <int COUT>
-__global__ __launch_bounds__(256) void bgrad_partial_kernel(const _Float16 *__restrict__ dZ, int M, int rows,
-                                                            float *__restrict__ partial) {
-    constexpr int CG = COUT / 8, RL = 256 / CG;  // 8-channel groups per row, row lanes
-    static_assert(COUT % 8 == 0 && 256 % CG == 0, "whole 16-byte groups");
-    __shared__ float red[RL][COUT + 1];
-    const int t = threadIdx.x, g = t % CG, rl = t / CG;
-    const int m0 = blockIdx.x * rows, m1 = min(M, m0 + rows);
-    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int m = m0 + rl; m < m1; m += RL) {
-        const v8h x = *reinterpret_cast<const v8h *>(dZ + (size_t)m * COUT + 8 * g);
-#pragma unroll
-        for (int i = 0; i < 8; i++) s[i] += (float)x[i];
-    }
-#pragma unroll
-    for (int i = 0; i < 8; i++) red[rl][8 * g + i] = s[i];
-    __syncthreads();
-    if (t < COUT) {
-        float a = 0.f;
-        for (int r = 0; r < RL; r++) a += red[r][t];
-        partial[(size_t)blockIdx.x * COUT + t] = a;
-    }
-}
-
-// Bias gradient, second level: each channel's partials over RL lanes, the lanes in a fixed
-// order, the gradient scale undone.
-template <int COUT>
-__global__ __launch_bounds__(256) void bgrad_final_kernel(const float *__restrict__ partial, int n_part,
-                                                          const float *__restrict__ scale, int slot,
-                                                          float *__restrict__ grad, int off) {
-    constexpr int RL = 256 / COUT;
-    __shared__ float red[256];
-    const int t = threadIdx.x, co = t % COUT, rl = t / COUT;
-    float s = 0.f;
-#pragma unroll 8
-    for (int q = rl; q < n_part; q += RL) s += partial[(size_t)q * COUT + co];
-    red[t] = s;
-    __syncthreads();
-    if (t < COUT) {
-        float a = 0.f;
-#pragma unroll
-        for (int r = 0; r < RL; r++) a += red[r * COUT + t];
-        grad[off + t] = a / scale[slot];
-    }
 }
 
 // Data gradient of a convolution, masked by the previous ReLU:
@@ -478,18 +498,25 @@ __device__ __forceinline__ int frag_index(int j, int J, int tap, int k, int K) {
     return (f * 64 + lane) * 8 + k % 8;
 }
 
-// FP16 copies of the convolution weights in fragment order: outputs co over padded inputs ci (the
-// forward pass), and outputs ci over inputs co (the data gradient).
-__global__ __launch_bounds__(256) void pack_weights_kernel(const float *__restrict__ w, int cout, int cin, int cinp,
-                                                           _Float16 *__restrict__ w16, _Float16 *__restrict__ wt16) {
-    const int e = blockIdx.x * 256 + threadIdx.x;
+// FP16 copies of the convolution weights in fragment order, layer blockIdx.y: outputs co over padded
+// inputs ci (the forward pass), and outputs ci over inputs co (the data gradient, layers 2 and 3).
+struct PackArgs {
+    const float *w[3];
+    _Float16 *w16[3], *wt16[3];
+};
+__device__ constexpr int PACK_CIN[3] = {33, 32, 64}, PACK_CINP[3] = {48, 32, 64}, PACK_COUT[3] = {32, 64, 32};
+constexpr int PACK_MAX = 32 * 9 * 64;  // weights of the largest layer, padded
+__global__ __launch_bounds__(256) void pack_weights_kernel(PackArgs a) {
+    const int l = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x;
+    const int cin = PACK_CIN[l], cinp = PACK_CINP[l], cout = PACK_COUT[l];
+    const float *w = a.w[l];
     if (e < cout * 9 * cinp) {
         const int co = e / (9 * cinp), rem = e % (9 * cinp), tap = rem / cinp, ci = rem % cinp;
-        w16[frag_index(co, cout, tap, ci, cinp)] = ci < cin ? (_Float16)w[(co * cin + ci) * 9 + tap] : (_Float16)0;
+        a.w16[l][frag_index(co, cout, tap, ci, cinp)] = ci < cin ? (_Float16)w[(co * cin + ci) * 9 + tap] : (_Float16)0;
     }
-    if (wt16 && e < cin * 9 * cout) {
+    if (l > 0 && e < cin * 9 * cout) {
         const int ci = e / (9 * cout), rem = e % (9 * cout), tap = rem / cout, co = rem % cout;
-        wt16[frag_index(ci, cin, tap, co, cout)] = (_Float16)w[(co * cin + ci) * 9 + tap];
+        a.wt16[l][frag_index(ci, cin, tap, co, cout)] = (_Float16)w[(co * cin + ci) * 9 + tap];
     }
 }
 
@@ -517,7 +544,7 @@ struct nbsi_net {
     std::vector<void *> owned;
     float *theta = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr, *scale = nullptr;
     float *feat = nullptr, *logits = nullptr, *dz = nullptr, *lossb = nullptr, *a3 = nullptr, *dA = nullptr,
-          *partial = nullptr;
+          *partial = nullptr, *bias_partial = nullptr;
     unsigned *maxbits = nullptr;
     _Float16 *w16[3] = {}, *wt16[3] = {}, *a1 = nullptr, *a2 = nullptr, *dZ = nullptr;
     bool packed = false;
@@ -556,14 +583,10 @@ struct NetDevice {  // current-device guard
 };
 
 hipError_t pack_weights(nbsi_net *net, hipStream_t st) {
-    const int dims[3][3] = {{33, 48, 32}, {32, 32, 64}, {64, 64, 32}};
-    const int offs[3] = {OFF_W1, OFF_W2, OFF_W3};
-    for (int l = 0; l < 3; l++) {
-        const int cin = dims[l][0], cinp = dims[l][1], cout = dims[l][2];
-        const long n = std::max((long)cout * 9 * cinp, (long)cin * 9 * cout);
-        hipLaunchKernelGGL(pack_weights_kernel, dim3(blocks(n)), dim3(256), 0, st, net->theta + offs[l], cout, cin,
-                           cinp, net->w16[l], l ? net->wt16[l] : nullptr);
-    }
+    const PackArgs a = {{net->theta + OFF_W1, net->theta + OFF_W2, net->theta + OFF_W3},
+                        {net->w16[0], net->w16[1], net->w16[2]},
+                        {nullptr, net->wt16[1], net->wt16[2]}};
+    hipLaunchKernelGGL(pack_weights_kernel, dim3(blocks(PACK_MAX), 3), dim3(256), 0, st, a);
     net->packed = true;
     return hipGetLastError();
 }
@@ -601,19 +624,14 @@ void weight_grads(nbsi_net *net, const _Float16 *x, const int32_t *index, int n_
     const int ks = ksplit_for(M);
     const int chunk = (M + ks - 1) / ks;
     constexpr int KT = (9 * CINP + 31) / 32;
-    hipLaunchKernelGGL((wgrad_kernel<CIN, CINP, COUT, IN_STAMP>), dim3(blocks((COUT / 32) * KT, 4), ks), dim3(256), 0,
-                       st, (const _Float16 *)net->dZ, x, index, n_stamps, n, chunk, net->partial);
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(blocks(COUT * 9 * CINP, 64)), dim3(256), 0, st, net->partial, ks, COUT,
-                       CIN, CINP, net->scale, slot, grad, off_w);
-    // the bias partials (up to BIAS_PARTS per channel) reuse the weight partials' buffer, which
-    // the reduction above has read
-    static_assert(256 % COUT == 0 && (size_t)BIAS_PARTS * COUT <= PARTIAL_FLOATS, "bias partials");
     const int n_part = std::max(1, std::min(BIAS_PARTS, M / 64));
     const int rows = (M + n_part - 1) / n_part;
-    hipLaunchKernelGGL(bgrad_partial_kernel<COUT>, dim3(n_part), dim3(256), 0, st, (const _Float16 *)net->dZ, M, rows,
-                       net->partial);
-    hipLaunchKernelGGL(bgrad_final_kernel<COUT>, dim3(1), dim3(256), 0, st, net->partial, n_part, net->scale, slot,
-                       grad, off_b);
+    const unsigned gx = blocks((COUT / 32) * KT, 4);
+    hipLaunchKernelGGL((wgrad_kernel<CIN, CINP, COUT, IN_STAMP>), dim3(gx, ks + blocks(n_part, gx)), dim3(256), 0, st,
+                       (const _Float16 *)net->dZ, x, index, n_stamps, n, ks, chunk, net->partial, n_part, rows,
+                       net->bias_partial);
+    hipLaunchKernelGGL(wgrad_reduce_kernel<COUT>, dim3(blocks(COUT * 9 * CINP, 64) + 1), dim3(256), 0, st, net->partial,
+                       ks, CIN, CINP, net->scale, slot, grad, off_w, off_b, net->bias_partial, n_part);
 }
 
 // Backward pass after forward(..., labels): every parameter's gradient into grad.
@@ -621,9 +639,8 @@ hipError_t backward(nbsi_net *net, const uint16_t *stamps, int n_stamps, const i
                     float *grad, hipStream_t st) {
     const int M = n * NPOS;
     const dim3 blk(256);
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, st, net->maxbits, 2, 0u);
-    hipLaunchKernelGGL(head_reduce_kernel, dim3(1), blk, 0, st, net->feat, net->dz, net->lossb, n, net->theta, grad,
-                       loss, net->scale);
+    hipLaunchKernelGGL(head_reduce_kernel, dim3(1), dim3(HR_NT), 0, st, net->feat, net->dz, net->lossb, n, net->theta,
+                       grad, loss, net->scale, net->maxbits);
     hipLaunchKernelGGL(dz3_kernel, dim3(blocks((long)M * 32)), blk, 0, st, net->a3, net->dz, net->theta, net->scale, n,
                        net->dZ);
     // layer 3 (input a2, 64 -> 32)
@@ -694,7 +711,8 @@ int nbsi_net_create(nbsi_ctx *ctx, const float *params_host, int max_batch, nbsi
     rc = rc ? rc : net_alloc(net, B, &net->lossb);
     rc = rc ? rc : net_alloc(net, B * NPOS * 32, &net->a3);
     rc = rc ? rc : net_alloc(net, B * NPOS * 64, &net->dA);
-    rc = rc ? rc : net_alloc(net, PARTIAL_FLOATS, &net->partial);
+    rc = rc ? rc : net_alloc(net, PARTIAL_FLOATS + (size_t)BIAS_PARTS * 64, &net->partial);
+    if (!rc) net->bias_partial = net->partial + PARTIAL_FLOATS;
     rc = rc ? rc : net_alloc(net, (size_t)2, &net->maxbits);
     rc = rc ? rc : net_alloc(net, B * NPOS * 32, &net->a1);
     rc = rc ? rc : net_alloc(net, B * NPOS * 64, &net->a2);
