@@ -3,9 +3,9 @@
 // point-spread function, and flags for extended morphology and deviant image noise.
 //
 // One wavefront fits one cutout in FP64: each lane holds up to two pixels of the (2h+1)^2 cutout
-// (h <= 5), the normal equations (28 + 7 sums) are reduced across the wave with butterflies so
-// every lane holds the same totals, and every lane then runs the same 7 x 7 Cholesky solve of the
-// Levenberg-Marquardt step.  The work per candidate is tiny next to the imaging that produced the
+// (h <= 5), the 36 sums of the normal equations are scattered over the lanes as they are reduced
+// and read back from LDS, so every lane holds the same totals, and every lane then runs the same
+// 7 x 7 Cholesky solve of the Levenberg-Marquardt step.  The work per candidate is tiny next to the imaging that produced the
 // cube; the kernel is latency-bound and exists so that the cuts run where the images live.
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -31,17 +31,52 @@ __device__ __forceinline__ double dpp_move(double v) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// Wave sum that leaves the same (bitwise) total in every lane: within rows of 16 lanes by DPP
-// (pair swap, quad half swap, half-row mirror, row mirror: each partner holds the other half's
-// partial sum), then across rows by lane shuffles.
-__device__ __forceinline__ double wsum(double v) {
-    v += dpp_move<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-    v += dpp_move<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-    v += dpp_move<0x141>(v);  // row_half_mirror
-    v += dpp_move<0x140>(v);  // row_mirror
-    v += __shfl_xor(v, 16, 64);
-    v += __shfl_xor(v, 32, 64);
-    return v;
+// The double of lane ^ BIT.
+template <int BIT>
+__device__ __forceinline__ double lane_xor(double v) {
+    if constexpr (BIT == 1) return dpp_move<0xB1>(v);       // quad_perm [1, 0, 3, 2]
+    else if constexpr (BIT == 2) return dpp_move<0x4E>(v);  // quad_perm [2, 3, 0, 1]
+    else if constexpr (BIT == 8) return dpp_move<0x128>(v); // row_ror:8
+    else if constexpr (BIT == 4) {                          // row_shl:4 into even banks, row_shr:4 into odd ones
+        const long long b = __double_as_longlong(v);
+        int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x104, 0xF, 0x5, false);
+        int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x104, 0xF, 0x5, false);
+        lo = __builtin_amdgcn_update_dpp(lo, (int)b, 0x114, 0xF, 0xA, false);
+        hi = __builtin_amdgcn_update_dpp(hi, (int)(b >> 32), 0x114, 0xF, 0xA, false);
+        return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+    } else {
+        return __shfl_xor(v, BIT, 64);
+    }
+}
+
+// Sums of N values over the wave.  Each level halves the values a lane carries: of a pair, lanes
+// with the level's bit clear keep the first and add the partner's, the others the second; a value
+// without a pair is summed in both.  Every sum is the balanced tree over the lanes (1, 2, 4, .. 32),
+// whatever lane it ends in, so the result does not depend on N.  Returns lane l's sum; the sum of
+// value q stands in lane sum_lane(q, N).
+template <int N, int BIT = 1>
+__device__ __forceinline__ double wave_sums(const double (&q)[N], int lane) {
+    if constexpr (BIT == 64) {
+        return q[0];
+    } else {
+        constexpr int H = (N + 1) / 2;
+        const bool up = (lane & BIT) != 0;
+        double r[H];
+#pragma unroll
+        for (int i = 0; i < H; i++) {
+            if (2 * i + 1 < N) {
+                const double a = q[2 * i], b = q[2 * i + 1];  // (values: a choice of addresses would go to memory)
+                const double keep = up ? b : a, give = up ? a : b;
+                r[i] = keep + lane_xor<BIT>(give);
+            } else {
+                r[i] = q[2 * i] + lane_xor<BIT>(q[2 * i]);
+            }
+        }
+        return wave_sums<H, BIT * 2>(r, lane);
+    }
+}
+__host__ __device__ constexpr int sum_lane(int q, int n, int bit = 1) {
+    return bit == 64 ? 0 : ((q & 1) && q < n ? bit : 0) + sum_lane(q / 2, (n + 1) / 2, bit * 2);
 }
 
 // Orders LDS accesses of one wavefront: writes before the call are visible to every lane of the
@@ -52,6 +87,7 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+constexpr int NQ = 28 + NP + 1;  // sums of the normal equations
 struct Normal {
     double h[28];  // upper triangle of J^T J, row-major
     double g[NP];  // J^T r
@@ -61,9 +97,10 @@ struct Normal {
 __device__ __forceinline__ int tri(int i, int j) { return i * NP - i * (i - 1) / 2 + (j - i); }  // i <= j
 
 // Model f = bkg + amp exp(-Q/2), Q = a dx^2 + 2 b dx dy + c dy^2 at the lane's pixels; residual
-// r = f - d.  Accumulates the lane's share of J^T J, J^T r and RSS and reduces them over the wave.
+// r = f - d.  Accumulates the lane's share of J^T J, J^T r and RSS and sums them over the wave (s_sum:
+// NQ doubles of LDS of this wave; slot: the sum that ends in this lane, or -1).
 __device__ void normal_eq(const double p[NP], const double px[2], const double py[2], const double d[2],
-                          const bool on[2], Normal &ne) {
+                          const bool on[2], double *s_sum, int slot, Normal &ne) {
 #pragma unroll
     for (int k = 0; k < 28; k++) ne.h[k] = 0.0;
 #pragma unroll
@@ -92,11 +129,22 @@ __device__ void normal_eq(const double p[NP], const double px[2], const double p
         }
         rss += r * r;
     }
+    double q[NQ];
 #pragma unroll
-    for (int k = 0; k < 28; k++) ne.h[k] = wsum(ne.h[k]);
+    for (int k = 0; k < 28; k++) q[k] = ne.h[k];
 #pragma unroll
-    for (int k = 0; k < NP; k++) ne.g[k] = wsum(ne.g[k]);
-    ne.rss = wsum(rss);
+    for (int k = 0; k < NP; k++) q[28 + k] = ne.g[k];
+    q[NQ - 1] = rss;
+    // every lane gets all sums, through LDS (as scalars they do not fit: 72 registers per set)
+    const double sum = wave_sums<NQ>(q, threadIdx.x & 63);
+    wave_sync();  // (the previous sums have been read)
+    if (slot >= 0) s_sum[slot] = sum;
+    wave_sync();
+#pragma unroll
+    for (int k = 0; k < 28; k++) ne.h[k] = s_sum[k];
+#pragma unroll
+    for (int k = 0; k < NP; k++) ne.g[k] = s_sum[28 + k];
+    ne.rss = s_sum[NQ - 1];
 }
 
 // In-place Cholesky M = L L^T of a packed symmetric matrix (L stored in the same upper-triangle
@@ -207,10 +255,21 @@ struct FitArgs {
     double *beam_out;            // [n][3] or null
 };
 
+// One candidate per workgroup of one wave.  A fit (300 steps at most) is a serial chain of FP64
+// exponentials, sums, a 7 x 7 factorisation and its square roots and divisions; with the state of a
+// step in registers one wave runs per SIMD and nothing hides that latency, so the instructions of
+// a step are what counts.  4096 candidates on 256 x 256 images: 2.20 ms with a butterfly per sum,
+// 1.51 ms with wave_sums.  Reading the totals with readlane spills scalar registers (3.22 ms),
+// two waves per SIMD spill vector registers (2.44 ms), and keeping the normal equations in LDS
+// between the steps lengthens the chain (1.54 ms).
 __global__ __launch_bounds__(64 * S2_WAVES) void gauss_fit_kernel(FitArgs A) {
     __shared__ float s_cut[S2_WAVES][128];
     __shared__ double s_med[S2_WAVES][2];
+    __shared__ __attribute__((aligned(16))) double s_sum[S2_WAVES][NQ];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int slot = -1;
+#pragma unroll
+    for (int q = 0; q < NQ; q++) slot = lane == sum_lane(q, NQ) ? q : slot;
     const int k = blockIdx.x * S2_WAVES + wave;
     if (k >= A.n) return;  // the whole wave leaves together
     const int h = A.half, w = 2 * h + 1, npx = w * w, n_pix = A.n_pix;
@@ -296,7 +355,7 @@ __global__ __launch_bounds__(64 * S2_WAVES) void gauss_fit_kernel(FitArgs A) {
 
     double p[NP] = {dc - B0, 0.0, 0.0, 1.0 / (sigma0 * sigma0), 0.0, 1.0 / (sigma0 * sigma0), B0};
     Normal cur, nxt;
-    normal_eq(p, px, py, d, on, cur);
+    normal_eq(p, px, py, d, on, s_sum[wave], slot, cur);
     // Levenberg-Marquardt with damping lambda * D, D = the largest diagonal of J^T J seen so far
     // (scale invariant, as in MINPACK), and the gain-ratio update of the damping of Nielsen
     // (Madsen, Nielsen & Tingleff, "Methods for non-linear least squares problems", 2004).
@@ -336,7 +395,7 @@ __global__ __launch_bounds__(64 * S2_WAVES) void gauss_fit_kernel(FitArgs A) {
             pn[i] = p[i] + dl[i];
             small = small && fabs(dl[i]) <= 1e-15 * (fabs(p[i]) + 1e-15);
         }
-        normal_eq(pn, px, py, d, on, nxt);
+        normal_eq(pn, px, py, d, on, s_sum[wave], slot, nxt);
         if (isfinite(nxt.rss) && nxt.rss < cur.rss) {
             const double rho = pred > 0.0 ? (cur.rss - nxt.rss) / pred : 0.0;
             const double t = 2.0 * rho - 1.0;
