@@ -424,12 +424,12 @@ __device__ __forceinline__ StageIn stage_load(int item, const float2 *__restrict
 // values of A, the 8 column weights with a zero row below them, and the first footprint column; a
 // lane's column weight is row min(col - first column, 8) of that table, so entries that miss the
 // block (the ranges hold for every frequency of the plan) add zeros.
-// Bound by the matrix pipe (about 40 of its cycles per step, U + 1 steps per block and round) and by
-// the staging's LDS stores and kernel evaluations; the vector form below, where a thread owns 16
-// cells, reads 8 weights and forms 8 products per baseline and cell block and spends half of its
-// multiply-adds outside the footprints.  4,096 channels of 256^2, 8,046 pairs: the image call took
-// 3.30 ms with the vector form and 2.97 with this one; without this loop it takes 2.1 (transforms,
-// staging, column pass).  U = 2: the straight run covers two thirds of a block's entries; U = 3 and
+// Bound by the dependent steps of a block (two LDS reads, then a product of 32 matrix cycles; the
+// matrix pipe is busy for 15% of the row pass) and by the staging's LDS stores and kernel
+// evaluations; the vector form below, where a thread owns 16 cells, reads 8 weights and forms 8
+// products per baseline and cell block and spends half of its multiply-adds outside the footprints.
+// 4,096 channels of 256^2, 8,046 pairs: the image call took 3.30 ms with the vector form and 2.97
+// with this one; without this loop it takes 2.1 (transforms, staging, column pass).  U = 2: the straight run covers two thirds of a block's entries; U = 3 and
 // 4 add zero products (3.00, 3.2 ms), four- and eight-byte wide reads of A need aligned starts and
 // lose as much again (3.07, 3.21), and products skipped one by one behind common reads are slower
 // (3.38).  Bands of four rows (512 x 512 images and up) half fill A: 1.71 against 1.47 ms for 300
