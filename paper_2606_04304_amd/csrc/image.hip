@@ -429,12 +429,12 @@ __device__ __forceinline__ StageIn stage_load(int item, const float2 *__restrict
 // evaluations; the vector form below, where a thread owns 16 cells, reads 8 weights and forms 8
 // products per baseline and cell block and spends half of its multiply-adds outside the footprints.
 // 4,096 channels of 256^2, 8,046 pairs: the image call took 3.30 ms with the vector form and 2.97
-// with this one; without this loop it takes 2.1 (transforms, staging, column pass).  U = 2: the straight run covers two thirds of a block's entries; U = 3 and
-// 4 add zero products (3.00, 3.2 ms), four- and eight-byte wide reads of A need aligned starts and
-// lose as much again (3.07, 3.21), and products skipped one by one behind common reads are slower
-// (3.38).  Bands of four rows (512 x 512 images and up) half fill A: 1.71 against 1.47 ms for 300
-// channels of 512^2, so they keep the vector form, as the FP16 and BF16 modes do, which round every
-// weighted value.
+// with this one; without this loop it takes 2.1 (transforms, staging, column pass).  U = 2: the
+// straight run covers two thirds of a block's entries; U = 3 and 4 add zero products (3.00, 3.2 ms),
+// four- and eight-byte wide reads of A need aligned starts and lose as much again (3.07, 3.21), and
+// products skipped one by one behind common reads are slower (3.38).  Bands of four rows (512 x 512
+// images and up) half fill A: 1.71 against 1.47 ms for 300 channels of 512^2, so they keep the
+// vector form, as the FP16 and BF16 modes do, which round every weighted value.
 typedef float v4f __attribute__((ext_vector_type(4)));
 template <int N>
 struct IntC {
