@@ -106,8 +106,6 @@ int nbsi_scratch(nbsi_ctx *ctx, int slot, size_t bytes, void **ptr) {
     return NBSI_OK;
 }
 
-namespace {
-
 // the auxiliary stream (non-blocking, default priority) and the stage events of a context
 int nbsi_aux_stream(nbsi_ctx *ctx) {
     if (ctx->aux) return NBSI_OK;
@@ -124,6 +122,8 @@ int nbsi_aux_stream(nbsi_ctx *ctx) {
     ctx->aux = s;
     return NBSI_OK;
 }
+
+namespace {
 
 int check_image_stokes(nbsi_ctx *ctx, const nbsi_image_plan *plan, int precision, const char *who) {
     if (plan->device != ctx->device) return nbsi_fail(ctx, NBSI_EINVAL, std::string(who) + ": plan built on another device");

@@ -224,6 +224,7 @@ hipError_t launch_image_grid(const nbsi_image_plan *p, const void *vis, int vis_
                              unsigned *flags = nullptr);
 hipError_t launch_image_grid_stokes(const nbsi_image_plan *p, const float2 *cvis, int precision, float2 *inter,
                                     float *img, hipStream_t st, unsigned *flags = nullptr);
+int nbsi_aux_stream(nbsi_ctx *ctx);  // creates the auxiliary stream and its events on first use
 hipError_t launch_detect_stats(const float *img, int n_chan, int n_pix, int mode, float *stats,
                                hipStream_t st);
 hipError_t launch_detect_scan(const float *img, int n_chan, int n_pix, int mode,

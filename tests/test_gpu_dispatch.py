@@ -147,3 +147,32 @@ def test_net_row_groups(n):
         assert torch.equal(net.forward(x, index=order), z[order.long()])
     assert torch.equal(net.forward(x[n - 1:].clone()), z[n - 1:])
     net.close()
+
+
+@pytest.mark.parametrize("half", [2, 5])
+def test_stage2_fits_beside_the_statistics(half):
+    """2^22 voxels take the two-stream form, half of them the single sequence.  The same 512
+    channels twice over have the same noise median, so the records are the same, bit for bit."""
+    g = torch.Generator(device="cpu").manual_seed(half)
+    n_chan, n_pix = 512, 64
+    cube = torch.randn((n_chan, n_pix, n_pix), generator=g)
+    cube[7] *= 9.0  # a channel of deviant noise
+    yy, xx = torch.meshgrid(torch.arange(n_pix), torch.arange(n_pix), indexing="ij")
+    cands = []
+    for i, (x, y, c, width) in enumerate([(20, 30, 3, 1.2), (33, 31, 7, 1.2), (40, 22, 100, 4.0), (31, 32, 511, 0.6),
+                                          (0, 5, 9, 1.0), (63, 63, 10, 1.0), (30, 40, -1, 1.0)]):
+        if c >= 0:
+            cube[c] += 40.0 * torch.exp(-((xx - x) ** 2 + (yy - y) ** 2) / (2.0 * width ** 2))
+        cands.append([x, y, c, 1, 0])
+    cands = torch.tensor(cands * 40, dtype=torch.int32, device="cuda:0")
+    beam = torch.tensor([[2.8, 2.8, 0.0]], dtype=torch.float64, device="cuda:0").repeat(2 * n_chan, 1)
+    one = cube.to("cuda:0")
+    two = torch.cat([one, one])
+    assert two.numel() == 1 << 22
+    want = nb.fits_host(nb.nbsi_stage2(one, cands, beam[:n_chan].contiguous(), half=half), len(cands))
+    for _ in range(2):  # the second call finds the first one's statistics in the scratch
+        got = nb.fits_host(nb.nbsi_stage2(two, cands, beam, half=half), len(cands))
+        assert got.tobytes() == want.tobytes()
+    flags = want["flags"][:7]
+    assert flags[1] & 4 and not flags[0] & 4 and flags[2] & 2 and all(flags[4:] & 8)
+    assert np.isfinite(want["chi2_red"][:4]).all() and np.isnan(want["chi2_red"][4:7]).all()
