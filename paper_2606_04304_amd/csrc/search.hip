@@ -449,10 +449,10 @@ __global__ __launch_bounds__(64) void search_width_kernel(const float *__restric
 }
 
 // Appends every in-horizon voxel with lo <= S < hi: append(i, channel, pixel, S) with i counted up
-// from *counter, one atomic per tile that holds any.  Returns the lane's smallest S taken.  A wave
-// takes tpw <= 64 tiles, reads their maxima and visits the tiles that reach lo (a pass over the S
-// cube took 0.30 ms at 4,096 x 256^2; a search's threshold lies in a few thousand of its 131,072
-// tiles).
+// from *counter, one atomic per tile that holds any.  Returns the lane's smallest S taken (NaN: none;
+// +inf is a value like any other).  A wave takes tpw <= 64 tiles, reads their maxima and visits the
+// tiles that reach lo (a pass over the S cube took 0.30 ms at 4,096 x 256^2; a search's threshold
+// lies in a few thousand of its 131,072 tiles).
 template <typename F>
 __device__ __forceinline__ float append_voxels(const float *__restrict__ best, const float *__restrict__ tmax, int tpw,
                                                int n_chan, int n_pix, float lo, float hi, int *__restrict__ counter,
@@ -462,7 +462,7 @@ __device__ __forceinline__ float append_voxels(const float *__restrict__ best, c
     const int t0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * tpw;
     const bool have = lane < tpw && t0 + lane < n_tiles;
     unsigned long long todo = __ballot(have && tmax[have ? t0 + lane : 0] >= lo);
-    float least = INFINITY;
+    float least = NAN;
     while (todo) {
         const int tile = t0 + (int)__ffsll((long long)todo) - 1;
         todo &= todo - 1;
@@ -523,7 +523,7 @@ __global__ __launch_bounds__(256) void search_accept_kernel(const float *__restr
     });
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) least = fminf(least, __shfl_xor(least, o, 64));
-    if ((threadIdx.x & 63) == 0 && least < INFINITY) atomicMin(&cnt->min_key, order_key(least));
+    if ((threadIdx.x & 63) == 0 && least == least) atomicMin(&cnt->min_key, order_key(least));
 }
 
 // Suppression, one wave per provisional detection: it survives when no other provisional

@@ -176,3 +176,18 @@ def test_stage2_fits_beside_the_statistics(half):
     flags = want["flags"][:7]
     assert flags[1] & 4 and not flags[0] & 4 and flags[2] & 2 and all(flags[4:] & 8)
     assert np.isfinite(want["chi2_red"][:4]).all() and np.isnan(want["chi2_red"][4:7]).all()
+
+
+def test_search_infinite_detections_only():
+    """Every provisional detection infinite: the threshold is +inf (not NaN), and the survivor, whose
+    re-evaluated sum is infinite too, is kept."""
+    n_chan, n_pix = 300, 16
+    r = _cube(n_chan, n_pix, 5, sigma=0.1)
+    r[150, 8, 9] = np.inf
+    x = torch.from_numpy(r).to(DEV)
+    for cubes in (False, True):
+        rec, thr, k, _, _ = nb.nbsi_search(x, fdr_q=0.01, want_cubes=cubes)
+        # the windows of 100 channels that hold channel 150 stand at channels 101 .. 200; of equal
+        # SNRs the lowest channel survives
+        assert thr == np.inf and k == 100
+        assert rec[["x", "y", "c", "width"]].tolist() == [(9, 8, 101, 100)] and rec["snr"][0] == np.inf
