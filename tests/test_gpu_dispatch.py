@@ -11,7 +11,7 @@ from test_gpu_drift import test_dedoppler_matches_oracle as dedoppler_parity
 from test_gpu_net import _stamps
 from test_gpu_net import test_forward_matches_oracle as forward_parity
 from test_gpu_parity import _noise_vis, _rel, detect_parity
-from test_gpu_search import _check_bank, _cube
+from test_gpu_search import _check_bank, _cube, _expected_records
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -191,3 +191,22 @@ def test_search_infinite_detections_only():
         # SNRs the lowest channel survives
         assert thr == np.inf and k == 100
         assert rec[["x", "y", "c", "width"]].tolist() == [(9, 8, 101, 100)] and rec["snr"][0] == np.inf
+
+
+@pytest.mark.parametrize("n_chan,n_pix", [(150, 16), (640, 40)])
+def test_search_suppression_of_dense_detections(n_chan, n_pix):
+    """Nearly every voxel a provisional detection: waves of a few detections and of 64, the last wave
+    not full; the records against the oracle's suppression of the same SNRs and widths."""
+    print(f"search dense n_chan={n_chan} n_pix={n_pix}", flush=True)
+    r = _cube(n_chan, n_pix, n_chan)
+    rec, thr, k, S, W = nb.nbsi_search(torch.from_numpy(r).to(DEV), fdr_q=0.6, want_cubes=True)
+    assert k > (500000 if n_chan > 600 else 20000)
+    Sg, Wg = (v.cpu().numpy().reshape(n_chan, -1).astype(t) for v, t in ((S, np.float64), (W, np.int32)))
+    exp = _expected_records(r, Sg, Wg, thr, n_pix)
+    got = {(int(a["x"]), int(a["y"]), int(a["c"])): int(a["width"]) for a in rec}
+    assert len(got) == len(rec) and set(got) <= set(exp)
+    for (x, y, c), snr2 in exp.items():
+        if abs(snr2 - thr) < 1e-4 * max(1.0, thr):
+            continue  # a float32 re-evaluation may fall on either side of the threshold
+        assert ((x, y, c) in got) == (snr2 >= thr)
+        assert (x, y, c) not in got or got[(x, y, c)] == Wg[c, y * n_pix + x]
