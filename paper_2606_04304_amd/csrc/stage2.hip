@@ -527,8 +527,11 @@ hipError_t launch_fit(const FitArgs &a, hipStream_t st) {
 bool fits_beside_noise(nbsi_ctx *ctx, size_t n_vox) {
     if (n_vox < S2_BESIDE_VOX) return false;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
-    return nbsi_aux_stream(ctx) == NBSI_OK;
+    const hipError_t e = hipStreamIsCapturing(ctx->stream, &cap);
+    if (e == hipSuccess && cap != hipStreamCaptureStatusNone) return false;
+    if (e == hipSuccess && nbsi_aux_stream(ctx) == NBSI_OK) return true;
+    (void)hipGetLastError();  // the sequence needs neither: its launches' checks are not to find this error
+    return false;
 }
 
 }  // namespace

@@ -210,3 +210,32 @@ def test_search_suppression_of_dense_detections(n_chan, n_pix):
             continue  # a float32 re-evaluation may fall on either side of the threshold
         assert ((x, y, c) in got) == (snr2 >= thr)
         assert (x, y, c) not in got or got[(x, y, c)] == Wg[c, y * n_pix + x]
+
+
+def test_stage2_captured_beside_eager():
+    """A captured nbsi_stage2 of 2^22 voxels keeps one sequence: every replay, with eager calls (which
+    take the two-stream form) and new inputs in between, equals the eager records."""
+    g = torch.Generator(device="cpu").manual_seed(3)
+    n_chan, n_pix = 1024, 64
+    cubes = [torch.randn((n_chan, n_pix, n_pix), generator=g).to(DEV) for _ in range(2)]
+    for q, cube in enumerate(cubes):
+        cube[5 + q] *= 9.0
+    cands = torch.tensor([[10 + 3 * i, 12 + 2 * i, 5 * i + 5, 1, 0] for i in range(16)] + [[1, 1, 6, 1, 0]],
+                         dtype=torch.int32, device=DEV)
+    beam = torch.tensor([[2.8, 2.8, 0.0]], dtype=torch.float64, device=DEV).repeat(n_chan, 1)
+    want = [nb.fits_host(nb.nbsi_stage2(cube, cands, beam), len(cands)).tobytes() for cube in cubes]
+    x, out = cubes[0].clone(), torch.zeros((len(cands), 160), dtype=torch.uint8, device=DEV)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        nb.nbsi_stage2(x, cands, beam, out=out)  # scratch is made before the capture
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        nb.nbsi_stage2(x, cands, beam, out=out)
+    for q in (0, 1, 0, 1):
+        x.copy_(cubes[q])
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert nb.fits_host(out, len(cands)).tobytes() == want[q]
+        assert nb.fits_host(nb.nbsi_stage2(cubes[1 - q], cands, beam), len(cands)).tobytes() == want[1 - q]
