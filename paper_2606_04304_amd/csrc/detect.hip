@@ -100,8 +100,9 @@ __device__ __forceinline__ float block_min_f(float v, float *red) {
     for (int q = 0; q < SEL_NW; q++) s = fminf(s, red[q]);
     return s;
 }
-// Mean over the waves of a wave-uniform value, in wave order (waves with ok false take no part).
-__device__ __forceinline__ float block_mean_f(float v, bool ok, float *red, int *ired) {
+// Mean over the waves of a wave-uniform value, in wave order (waves with ok false take no part;
+// none when no wave does).
+__device__ __forceinline__ float block_mean_f(float v, bool ok, float none, float *red, int *ired) {
     const int w = threadIdx.x >> 6;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) {
@@ -116,7 +117,7 @@ __device__ __forceinline__ float block_mean_f(float v, bool ok, float *red, int 
         s += red[q];
         n += ired[q];
     }
-    return s / (float)n;
+    return n ? s / (float)n : none;
 }
 __device__ __forceinline__ float block_max_f(float v, float *red) {
     v = wave_max_f(v);
@@ -269,7 +270,7 @@ __device__ __forceinline__ float block_select(Each each, float a, float b, int r
 // Median of the n values of a block (mean of the central pair for even n; exact order statistics).
 // smp is one of the thread's values (NaN: none).  Every wave sorts its 64 samples and proposes the
 // ones a few places either side of the rank's expected place; their means over the waves bracket
-// the rank among about a tenth of the values.  compact(a, b, below) lists the values inside [a, b]
+// the rank among about a tenth of the values (no samples at all: every finite value).  compact(a, b, below) lists the values inside [a, b]
 // in LDS, per wave and without atomics, and counts those below a: one pass over all values, after
 // which the selection runs over the listed ones (list(f)).  It returns how many it listed, or -1
 // when it could not; then, or when the bracket missed the rank, the selection runs over all values.
@@ -283,8 +284,8 @@ __device__ __forceinline__ float block_median(Each each, Compact compact, List l
     const int s_n = __popcll(__ballot(smp < INFINITY));
     const int p = (int)(((long long)rank * s_n) / n);
     const float pa = __shfl(srt, max(p - D, 0), 64), pb = __shfl(srt, min(p + D, max(s_n - 1, 0)), 64);
-    const float a = block_mean_f(pa, s_n > 0, L.fred, L.ired);
-    const float b = block_mean_f(pb, s_n > 0, L.fred, L.ired);
+    const float a = block_mean_f(pa, s_n > 0, -__FLT_MAX__, L.fred, L.ired);
+    const float b = block_mean_f(pb, s_n > 0, __FLT_MAX__, L.fred, L.ired);
     int below = 0;
     const int n_in = compact(a, b, below);
     float vhi;
@@ -878,7 +879,7 @@ __global__ __launch_bounds__(SEL_NT) void image_stats_kernel(const float *__rest
     };
     // the thread's values, NaN where there is none (non-finite pixels take no part in the statistics)
     float v[NV ? NV : 1];
-    float smp = NAN;  // one of them, from the middle of its column
+    float smp = NAN;  // one of them, from the middle of its column if it can be
     if constexpr (NV > 0) {
         int y0 = 1, y1 = 0;
         if (on) rows(x0, y0, y1);
@@ -886,12 +887,17 @@ __global__ __launch_bounds__(SEL_NT) void image_stats_kernel(const float *__rest
 #pragma unroll
         for (int j = 0; j < NV; j++)  // (rows past the last read it again: no branch, all loads in flight)
             v[j] = im[(nv ? y0 + min(j, nv - 1) * G : h) * n_pix + min(x0, n_pix - 1)];
+        float any = NAN;
 #pragma unroll
         for (int j = 0; j < NV; j++) {
             v[j] = j < nv && __builtin_isfinite(v[j]) ? v[j] : NAN;
-            // (lane l samples around its own place, so that a wave's samples spread over the image)
+            any = v[j] == v[j] ? v[j] : any;
+            // (lane l samples around its own place, so that a wave's samples spread over the image; on
+            // 8 x 8 images such places have no value, and without the others a call on 2,000 of them
+            // took 0.39 ms instead of 0.18)
             smp = (j & 7) == (t & 7) && v[j] == v[j] && (j <= nv / 2 + 4 || smp != smp) ? v[j] : smp;
         }
+        smp = smp == smp ? smp : any;
     } else if (on && x0 < n_pix) {
         int y0, y1;
         rows(x0, y0, y1);

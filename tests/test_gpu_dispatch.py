@@ -239,3 +239,48 @@ def test_stage2_captured_beside_eager():
         torch.cuda.synchronize()
         assert nb.fits_host(out, len(cands)).tobytes() == want[q]
         assert nb.fits_host(nb.nbsi_stage2(cubes[1 - q], cands, beam), len(cands)).tobytes() == want[1 - q]
+
+
+@pytest.mark.parametrize("n_pix", [8, 64, 128, 136, 256, 264])
+def test_image_statistics_every_image_observed(n_pix):
+    """Medians and MADs of images that are hard to select from, through the per-image SNRs of every
+    searched pixel: ties, ramps, outliers, a range wider than the largest float, subnormal values,
+    NaN and infinite pixels, and no finite pixel where the samples are taken."""
+    print(f"image statistics observed n_pix={n_pix}", flush=True)
+    rng = np.random.default_rng(100 + n_pix)
+    n_chan, h = 13, n_pix // 2
+    cube = rng.standard_normal((n_chan, n_pix, n_pix)).astype(np.float32)
+    cube[1] = rng.integers(-2, 3, (n_pix, n_pix))
+    cube[2] = 7.5
+    cube[3] = np.arange(n_pix * n_pix, dtype=np.float32).reshape(n_pix, n_pix)
+    cube[4] = -cube[3].T
+    with np.errstate(over="ignore"):
+        cube[5] *= np.float32(1e38)
+    cube[6] *= np.float32(1e-41)
+    cube[7, ::3, ::2] = 1e30
+    cube[8, rng.random((n_pix, n_pix)) < 0.4] = np.nan
+    cube[9, ::4] = np.inf
+    cube[10] = np.exp(4.0 * cube[10])
+    cube[11, h:h + 2] = np.nan
+    _, snr, _ = nb.nbsi_detect(torch.from_numpy(cube).to(DEV), mode=nb.NBSI_DETECT_PER_IMAGE, want_snr=True)
+    ref, valid = oracle.detect.snr_cube(cube, "per_image")
+    got = snr.cpu().numpy().astype(np.float64)
+    assert valid.sum() > n_pix * n_pix // 8 and np.all(got[:, ~valid] == 0.0)
+    mask = oracle.detect.horizon_mask(n_pix)
+    z = ref[:, valid]
+    tol = np.zeros_like(z)
+    for c in range(n_chan):
+        v = cube[c][mask].astype(np.float64)
+        v = v[np.isfinite(v)]
+        med = np.median(v)
+        sigma = 1.482602218505602 * np.median(np.abs(v - med))
+        assert (sigma > 0) == (c != 2)  # only the constant image has none
+        # float32 roundings of x - med, of the MAD and of the quotient, each relative to the values
+        # they are formed from; subnormal values are rounded to their spacing
+        x = np.abs(cube[c][valid].astype(np.float64))
+        unit = (2.0 ** -24 * (x + abs(med)) + 2.0 ** -149) / sigma if sigma > 0 else 0.0
+        tol[c] = 8.0 * (unit + 2.0 ** -24) * (1.0 + np.abs(z[c]))
+    # the pixel's median over the channels moves by no more than the values next to it
+    tol += np.where(np.abs(z) < 0.01, tol, 0.0).max(axis=0)
+    d = np.abs(got[:, valid] - z)
+    assert np.all(d <= tol), np.unravel_index(np.argmax(d - tol), d.shape)
