@@ -434,7 +434,11 @@ __device__ __forceinline__ StageIn stage_load(int item, const float2 *__restrict
 // four- and eight-byte wide reads of A need aligned starts and lose as much again (3.07, 3.21), and
 // products skipped one by one behind common reads are slower (3.38).  Bands of four rows (512 x 512
 // images and up) half fill A: 1.71 against 1.47 ms for 300 channels of 512^2, so they keep the
-// vector form, as the FP16 and BF16 modes do, which round every weighted value.
+// vector form, as the FP16 and BF16 modes do, which round every weighted value.  So do 64 x 64
+// images: their 8 column blocks leave a wave two, whose 4 (8 in tall bands) strips each read 1 KB of
+// A per step, and one block's products no longer cover another's reads: 304 against 279 us for 4,096
+// channels of 150 antennas over 300 m, 993 against 942 for 512 channels of 352 over 100 m as a batch
+// and 1.75 against 1.31 ms with tall bands.
 typedef float v4f __attribute__((ext_vector_type(4)));
 template <int N>
 struct IntC {
@@ -444,7 +448,7 @@ struct IntC {
 template <int LOGM, int GE>
 struct MfmaShape {
     using GS = GridShape<LOGM, GE>;
-    static constexpr bool OK = GS::R % 8 == 0;
+    static constexpr bool OK = GS::R % 8 == 0 && GS::M > 128;
     static constexpr int STRIPS = OK ? GS::R / 8 : 1;        // 8-row strips of the band
     static constexpr int BLOCKS = GS::M / 16;
     static constexpr int BPW = BLOCKS / 4;                   // blocks per wave
