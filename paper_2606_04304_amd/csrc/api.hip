@@ -606,6 +606,22 @@ int image_plan_build(nbsi_ctx *ctx, const double *ant_xyz_host, int n_ant, const
             band_off.push_back((int)band_items.size());
         }
         p->n_band_items = (int)band_items.size();
+        // Tall bands (32 cells per thread) of 256 x 256 images and up exist in both gridding forms.
+        // The matrix form's time follows the entries, a thread's of the vector form its busiest
+        // columns, so the vector form wins where the uv plane is filled evenly: where the longest
+        // block ranges of the bands hold less than 1 / 11 (512 columns) or 1 / 18 (1,024) of their
+        // entries.  A whole batch of 384 channels of 256^2, matrix and vector: 352 antennas over
+        // 300 m (1 / 16) 1.87 and 1.59 ms, over 100 m (1 / 7.5) 5.66 and 7.62, 150 over 300 m
+        // (1 / 13.6) 0.560 and 0.540, over 750 m (1 / 10.7) 0.371 and 0.379; of 512^2: 352 over 400 m
+        // (1 / 23.5) 3.40 and 3.05, over 200 m (1 / 13.9) 4.97 and 8.28, 150 over 300 m (1 / 15.5) 1.68
+        // and 1.78, 352 over 300 m (1 / 19.3) 4.09 and 4.08.
+        int64_t longest = 0;
+        for (int bnd = 0; bnd < p->n_bands; bnd++) {
+            int m = 0;
+            for (int b = 0; b < M / 16; b++) m = std::max(m, blk[(size_t)bnd * (M / 16) + b].y - blk[(size_t)bnd * (M / 16) + b].x);
+            longest += m;
+        }
+        p->grid_matrix = longest * (M >= 1024 ? 18 : 11) >= p->n_band_items;
         // 1 / Fourier transform of the ES kernel at image column x, frequency (x - n/2)/M cycles
         // per cell: Phi(f) = 4 int_{-1}^{1} phi(z) cos(8 pi z f) dz.
         std::vector<double> gx, gw;

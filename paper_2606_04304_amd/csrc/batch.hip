@@ -44,6 +44,7 @@ struct nbsi_batch {
         // single-band tiled kernel once per job (h_corr)
         int kind;
         int a = 0, b = 0;  // kind-specific shape (log_m/g, variant, log_m/ge)
+        bool matrix = true;  // rows: the gridding form (nbsi_image_plan::grid_matrix)
         int group = 0;     // sub-band group (one group per sub-band with NBSI_BATCH_OVERLAP)
         int n_jobs = 0, n_tasks = 0, max_dyn = 0;
         void *d_jobs = nullptr;
@@ -142,7 +143,7 @@ hipError_t launch_one(const nbsi_batch *b, const nbsi_batch::Launch &L, hipStrea
                                               b->n_in, st);
         case 2: return launch_correlate_batch((const CorrJob *)L.d_jobs, L.n_jobs, L.n_tasks, L.a, b->n_in, L.b != 0, st);
         case 3: return launch_image_batch_gather((const ImgJob *)L.d_jobs, L.n_jobs, L.n_tasks, st);
-        case 4: return launch_image_batch_rows((const ImgJob *)L.d_jobs, L.n_jobs, L.n_tasks, L.a, b->precision, L.b, st);
+        case 4: return launch_image_batch_rows((const ImgJob *)L.d_jobs, L.n_jobs, L.n_tasks, L.a, b->precision, L.b, L.matrix, st);
         case 5: return launch_image_batch_cols((const ImgJob *)L.d_jobs, L.n_jobs, L.n_tasks, L.a, L.b, st);
         case 6:
             for (const CorrJob &j : L.h_corr) {
@@ -310,13 +311,14 @@ int build_group_launches(nbsi_batch *b, const std::vector<int> &members, int gro
         j.uv_max = p->uv_max;
         j.flags = b->ctx->d_flags;
     }
-    // channel chunks of every sub-band of one (transform size, tile height), each chunk's row
-    // intermediate within IMAGE_CHUNK_BYTES: per chunk a gather, a rows and a columns launch, so
+    // channel chunks of every sub-band of one (transform size, tile height, gridding form), each chunk's
+    // row intermediate within IMAGE_CHUNK_BYTES: per chunk a gather, a rows and a columns launch, so
     // the Stokes-I gather and the intermediate are read back while still in the last-level cache
-    std::map<std::pair<int, int>, std::vector<int>> rg;
-    for (int s : members) rg[{base[s].log_m, b->grid_ge[s]}].push_back(s);
+    std::map<std::tuple<int, int, bool>, std::vector<int>> rg;
+    for (int s : members)
+        rg[{base[s].log_m, b->grid_ge[s], b->precision != NBSI_PREC_FP32 || b->plans[s]->grid_matrix}].push_back(s);
     for (auto &kv : rg) {
-        const int ge = kv.first.second;
+        const int log_m = std::get<0>(kv.first), ge = std::get<1>(kv.first);
         std::vector<ImgJob> chunk;
         size_t used = 0, cv_used = 0;  // bytes of the chunk's intermediate and Stokes-I gather
         auto flush = [&]() -> int {
@@ -340,8 +342,9 @@ int build_group_launches(nbsi_batch *b, const std::vector<int> &members, int gro
             b->launches.push_back(G);
             nbsi_batch::Launch R;
             R.kind = 4;
-            R.a = kv.first.first;
+            R.a = log_m;
             R.b = ge;
+            R.matrix = std::get<2>(kv.first);
             R.n_jobs = (int)rows.size();
             R.n_tasks = rt;
             int rc = upload(b, rows, (ImgJob **)&R.d_jobs);
@@ -349,7 +352,7 @@ int build_group_launches(nbsi_batch *b, const std::vector<int> &members, int gro
             b->launches.push_back(R);
             nbsi_batch::Launch C;
             C.kind = 5;
-            C.a = kv.first.first;
+            C.a = log_m;
             C.b = ge;
             C.n_jobs = (int)cols.size();
             C.n_tasks = ct;

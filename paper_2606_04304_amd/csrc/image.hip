@@ -437,8 +437,8 @@ __device__ __forceinline__ StageIn stage_load(int item, const float2 *__restrict
 // vector form, as the FP16 and BF16 modes do, which round every weighted value.  So do 64 x 64
 // images: their 8 column blocks leave a wave two, whose 4 (8 in tall bands) strips each read 1 KB of
 // A per step, and one block's products no longer cover another's reads: 304 against 279 us for 4,096
-// channels of 150 antennas over 300 m, 993 against 942 for 512 channels of 352 over 100 m as a batch
-// and 1.75 against 1.31 ms with tall bands.
+// channels of 150 antennas over 300 m, 1.08 against 0.97 ms of row pass for 512 channels of 352 over
+// 100 m.  In tall bands of 256 x 256 and 512 x 512 images the plan chooses (image_plan_build).
 typedef float v4f __attribute__((ext_vector_type(4)));
 template <int N>
 struct IntC {
@@ -449,6 +449,7 @@ template <int LOGM, int GE>
 struct MfmaShape {
     using GS = GridShape<LOGM, GE>;
     static constexpr bool OK = GS::R % 8 == 0 && GS::M > 128;
+    static constexpr bool PER_PLAN = OK && GE == 32 && GS::M >= 512;  // the plan says which form
     static constexpr int STRIPS = OK ? GS::R / 8 : 1;        // 8-row strips of the band
     static constexpr int BLOCKS = GS::M / 16;
     static constexpr int BPW = BLOCKS / 4;                   // blocks per wave
@@ -582,7 +583,7 @@ __device__ __forceinline__ void grid_band_mfma(const float2 *__restrict__ cv_c, 
     __syncthreads();
 }
 
-template <int LOGM, int PREC, int GE>
+template <int LOGM, int PREC, int GE, bool MFMA>
 __device__ __forceinline__ void grid_rows(const float2 *__restrict__ cvis, const double2 *__restrict__ dxy,
                                           const double *__restrict__ freq, const int *__restrict__ band_off,
                                           const int *__restrict__ band_items, const int2 *__restrict__ blk, int n_pairs,
@@ -602,8 +603,8 @@ __device__ __forceinline__ void grid_rows(const float2 *__restrict__ cvis, const
     const float2 *cv_c = cvis + (size_t)c * n_pairs;
     const int k_begin = band_off[band], k_end = band_off[band + 1];
     const int n_items = k_end - k_begin;
-    constexpr bool MFMA = PREC == NBSI_PREC_FP32 && MfmaShape<LOGM, GE>::OK;
     if constexpr (MFMA) {
+        static_assert(PREC == NBSI_PREC_FP32 && MfmaShape<LOGM, GE>::OK, "products and sums in FP32");
         grid_band_mfma<LOGM, GE>(cv_c, dxy, freq[c] / C_LIGHT * 4.0, band_items + k_begin, n_items,
                                  blk + (size_t)band * MfmaShape<LOGM, GE>::BLOCKS, bset, row0, c, grid, tab);
     } else {
@@ -755,7 +756,7 @@ __device__ __forceinline__ void grid_rows(const float2 *__restrict__ cvis, const
 
 // Row pass of the chunk's channels: XCD-aware order (all bands of a channel run on one XCD, so
 // its Stokes I row is read into one L2 once).
-template <int LOGM, int PREC, int GE>
+template <int LOGM, int PREC, int GE, bool MFMA>
 __global__ __launch_bounds__(256) void grid_rows_kernel(const float2 *__restrict__ cvis, const double2 *__restrict__ dxy,
                                                         const double *__restrict__ freq, const int *__restrict__ band_off,
                                                         const int *__restrict__ band_items, const int2 *__restrict__ blk,
@@ -768,12 +769,12 @@ __global__ __launch_bounds__(256) void grid_rows_kernel(const float2 *__restrict
     const int id = blockIdx.x, xcd = id & 7, slot = id >> 3;
     const int c = ((slot / GS::NB) << 3) + xcd, band = slot % GS::NB;
     if (c >= n_chan) return;
-    grid_rows<LOGM, PREC, GE>(cvis, dxy, freq, band_off, band_items, blk, n_pairs, bset, inter, band, c, grid, tab, vscale);
+    grid_rows<LOGM, PREC, GE, MFMA>(cvis, dxy, freq, band_off, band_items, blk, n_pairs, bset, inter, band, c, grid, tab, vscale);
 }
 
 // Gridding of channel ranges of several sub-bands of one image size: task -> (job, channel,
 // band), one workgroup per task.
-template <int LOGM, int PREC, int GE>
+template <int LOGM, int PREC, int GE, bool MFMA>
 __global__ __launch_bounds__(256) void grid_rows_batch_kernel(const ImgJob *__restrict__ jobs, int n_jobs,
                                                               int n_tasks) {
     using GS = GridShape<LOGM, GE>;
@@ -787,7 +788,7 @@ __global__ __launch_bounds__(256) void grid_rows_batch_kernel(const ImgJob *__re
     const ImgJob &jb = jobs[j];
     const int local = task - jb.rows_task0;
     const SetTest bset{jb.inb, (jb.n_pairs + 31) >> 5};
-    grid_rows<LOGM, PREC, GE>(jb.cvis, jb.dxy, jb.freq, jb.band_off, jb.band_items, jb.blk, jb.n_pairs, bset, jb.inter,
+    grid_rows<LOGM, PREC, GE, MFMA>(jb.cvis, jb.dxy, jb.freq, jb.band_off, jb.band_items, jb.blk, jb.n_pairs, bset, jb.inter,
                               local % GS::NB, local / GS::NB, grid, tab, vscale);
 }
 
@@ -957,12 +958,14 @@ static hipError_t launch_grid_m(const nbsi_image_plan *p, int precision, const f
     const int c8 = (p->n_chan + 7) / 8 * 8;  // XCD-aware order: eight channels per round of blocks
     const SetTest bset{p->d_inb, (p->n_pairs + 31) >> 5};
     const dim3 gr((unsigned)(GridShape<LOGM, GE>::NB * c8));
-#define NBSI_ROWS(PR)                                                                                           \
-    hipLaunchKernelGGL((grid_rows_kernel<LOGM, PR, GE>), gr, dim3(256), 0, st, cvis, p->d_dxy, p->d_freq,      \
+#define NBSI_ROWS(PR, MX)                                                                                       \
+    hipLaunchKernelGGL((grid_rows_kernel<LOGM, PR, GE, MX>), gr, dim3(256), 0, st, cvis, p->d_dxy, p->d_freq,  \
                        p->d_band_off, p->d_band_items, p->d_blk, p->n_pairs, p->n_chan, bset, inter)
-    if (precision == NBSI_PREC_FP16) NBSI_ROWS(NBSI_PREC_FP16);
-    else if (precision == NBSI_PREC_BF16) NBSI_ROWS(NBSI_PREC_BF16);
-    else NBSI_ROWS(NBSI_PREC_FP32);
+    using MS = MfmaShape<LOGM, GE>;
+    if (precision == NBSI_PREC_FP16) NBSI_ROWS(NBSI_PREC_FP16, false);
+    else if (precision == NBSI_PREC_BF16) NBSI_ROWS(NBSI_PREC_BF16, false);
+    else if (MS::PER_PLAN && !p->grid_matrix) NBSI_ROWS(NBSI_PREC_FP32, MS::OK && !MS::PER_PLAN);
+    else NBSI_ROWS(NBSI_PREC_FP32, MS::OK);
 #undef NBSI_ROWS
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1010,33 +1013,37 @@ hipError_t launch_image_batch_gather(const ImgJob *d_jobs, int n_jobs, int n_tas
     return hipGetLastError();
 }
 
+template <int LOGM, int GE>
+static void launch_batch_rows_m(const ImgJob *d_jobs, int n_jobs, int n_tasks, int precision, bool matrix, hipStream_t st) {
+    using MS = MfmaShape<LOGM, GE>;
+#define NBSI_BR(PR, MX)                                                                                            \
+    hipLaunchKernelGGL((grid_rows_batch_kernel<LOGM, PR, GE, MX>), dim3(n_tasks), dim3(256), 0, st, d_jobs, n_jobs, \
+                       n_tasks)
+    if (precision == NBSI_PREC_FP16) NBSI_BR(NBSI_PREC_FP16, false);
+    else if (precision == NBSI_PREC_BF16) NBSI_BR(NBSI_PREC_BF16, false);
+    else if (MS::PER_PLAN && !matrix) NBSI_BR(NBSI_PREC_FP32, MS::OK && !MS::PER_PLAN);
+    else NBSI_BR(NBSI_PREC_FP32, MS::OK);
+#undef NBSI_BR
+}
+
 template <int GE>
 static hipError_t launch_batch_rows_ge(const ImgJob *d_jobs, int n_jobs, int n_tasks, int log_m, int precision,
-                                       hipStream_t st) {
-#define NBSI_BR(LM, PR)                                                                                        \
-    hipLaunchKernelGGL((grid_rows_batch_kernel<LM, PR, GE>), dim3(n_tasks), dim3(256), 0, st, d_jobs, n_jobs, \
-                       n_tasks)
-#define NBSI_BR_P(LM)                                                    \
-    if (precision == NBSI_PREC_FP16) NBSI_BR(LM, NBSI_PREC_FP16);         \
-    else if (precision == NBSI_PREC_BF16) NBSI_BR(LM, NBSI_PREC_BF16);    \
-    else NBSI_BR(LM, NBSI_PREC_FP32)
+                                       bool matrix, hipStream_t st) {
     switch (log_m) {
-        case 7: NBSI_BR_P(7); break;
-        case 8: NBSI_BR_P(8); break;
-        case 9: NBSI_BR_P(9); break;
-        case 10: NBSI_BR_P(10); break;
-        case 11: NBSI_BR_P(11); break;
+        case 7: launch_batch_rows_m<7, GE>(d_jobs, n_jobs, n_tasks, precision, matrix, st); break;
+        case 8: launch_batch_rows_m<8, GE>(d_jobs, n_jobs, n_tasks, precision, matrix, st); break;
+        case 9: launch_batch_rows_m<9, GE>(d_jobs, n_jobs, n_tasks, precision, matrix, st); break;
+        case 10: launch_batch_rows_m<10, GE>(d_jobs, n_jobs, n_tasks, precision, matrix, st); break;
+        case 11: launch_batch_rows_m<11, GE>(d_jobs, n_jobs, n_tasks, precision, matrix, st); break;
         default: return hipErrorInvalidValue;
     }
-#undef NBSI_BR_P
-#undef NBSI_BR
     return hipGetLastError();
 }
 
 hipError_t launch_image_batch_rows(const ImgJob *d_jobs, int n_jobs, int n_tasks, int log_m, int precision, int ge,
-                                   hipStream_t st) {
-    return ge == 32 ? launch_batch_rows_ge<32>(d_jobs, n_jobs, n_tasks, log_m, precision, st)
-                    : launch_batch_rows_ge<16>(d_jobs, n_jobs, n_tasks, log_m, precision, st);
+                                   bool matrix, hipStream_t st) {
+    return ge == 32 ? launch_batch_rows_ge<32>(d_jobs, n_jobs, n_tasks, log_m, precision, matrix, st)
+                    : launch_batch_rows_ge<16>(d_jobs, n_jobs, n_tasks, log_m, precision, matrix, st);
 }
 
 template <int GE>

@@ -68,6 +68,7 @@ struct nbsi_image_plan {
     // [n_bands][2 n_pix / 16]: entries [x, y) of a band's list hold every item whose footprint can
     // reach grid columns 16 b .. 16 b + 15 at some frequency of the plan
     int2 *d_blk = nullptr;
+    bool grid_matrix = true;  // FP32 gridding where both forms exist: the matrix form
     float *d_corr = nullptr;      // [n_pix] 1 / (kernel Fourier transform) per image column
     // gridding plans: membership bitmap of B, [n_chan][(n_pairs + 31) / 32] words (bit k % 32 of
     // word k / 32 = pair k imaged at that channel), written by the count kernel
@@ -191,7 +192,7 @@ __host__ __device__ constexpr int cols_per_band(int ge, int n_pix) {
 
 hipError_t launch_image_batch_gather(const ImgJob *d_jobs, int n_jobs, int n_tasks, hipStream_t st);
 hipError_t launch_image_batch_rows(const ImgJob *d_jobs, int n_jobs, int n_tasks, int log_m, int precision, int ge,
-                                   hipStream_t st);
+                                   bool matrix, hipStream_t st);
 hipError_t launch_image_batch_cols(const ImgJob *d_jobs, int n_jobs, int n_tasks, int log_m, int ge, hipStream_t st);
 
 int channelize_log_m(int log_n, int n_chan);

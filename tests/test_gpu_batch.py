@@ -236,3 +236,32 @@ def test_batch_uneven_subbands_full_size():
             torch.cuda.synchronize()
             _same(b, ref)
         b.close()
+
+
+@pytest.mark.parametrize("n_pix", [256, 512])
+def test_batch_tall_bands_both_gridding_forms(n_pix):
+    """Tall bands of one image size whose uv plane is crowded in the middle (20 MHz) and filled evenly
+    (80 MHz): sub-bands of both gridding forms in one batch,
+    against the direct-Fourier oracle at sampled pixels."""
+    print(f"batch tall bands, both forms, n_pix={n_pix}", flush=True)
+    n_ant, n_fft, n_spec, n_chan = 200, 1024, 2, 3
+    xyz = synth.antenna_layout(n_ant, 400.0, 31)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n_pix)
+    subs = []
+    for nu0 in (20e6, 80e6, 20.5e6, 81e6):
+        v = torch.randint(-20, 21, (2 * n_ant, n_spec * n_fft, 2), generator=g, device=DEV, dtype=torch.int8)
+        gain = torch.full((2 * n_ant,), float(synth.gain_noise(n_fft, 12.0)), dtype=torch.float32, device=DEV)
+        subs.append(dict(volt=v, gain=gain, n_fft=n_fft, n_spec=n_spec, chan0=500, n_chan=n_chan, n_pix=n_pix,
+                         freq_hz=nu0 + 20.0 * np.arange(n_chan)))
+    b = nb.Batch(xyz, subs, grid_tall=True)
+    for rep in range(2):
+        _poison(b)
+        b.run()
+        torch.cuda.synchronize()
+        for d in b.subbands:
+            pix = np.random.default_rng(rep).integers(0, n_pix, (200, 2)).astype(np.int32)
+            ref = oracle.image_dft_pixels(d["vis"].cpu().numpy(), xyz, d["freq_hz"], n_pix, pix, grid_n_pix=n_pix)
+            got = d["img"].cpu().numpy().astype(np.float64)[:, pix[:, 1], pix[:, 0]]
+            assert np.abs(got - ref).max() / np.abs(ref).max() <= 1e-5
+    b.close()
