@@ -11,12 +11,13 @@
 // s needs channels c - S_s .. c + CQ - 1 + S_s, S_s = shift(D_MAX, s).  A step shifts the windows
 // down by CQ registers and appends the channels loaded while the previous step computed, so each
 // input value is read once per segment (plus its ends) and the 2D + 1 trials run from registers:
-// no LDS, no barriers.  Channels at least the requested drift from both band edges skip the band
-// tests (every track fits).
-// Bound by vector instructions (per voxel 33 x (multiply, compare, two selects) and ~70 additions,
-// partial sums shared by several trials being formed once).  4 x 4,096 x 256^2, 33 trials: 1.31 ms
-// (4.3 TB/s of the cubes in and the results out); 2.55 ms when the windows stood in LDS (67 reads per
-// voxel, and 1.5x the input through the halos).
+// no LDS, no barriers.  Channels outside the band stand in the windows as -inf, so that tracks which
+// leave the band need no test: with a test per trial, the segments at the band's ends set the time
+// of every small search (2 x 400 x 48^2, full range: 25.0 us a call; 21.5 with windows in LDS, 13.9 without the tests).
+// Bound by vector instructions (per voxel 33 x (compare, two selects; a multiply where 1 / sqrt(n_sub)
+// is not exact) and ~70 additions, partial sums shared by several trials being formed once).
+// 4 x 4,096 x 256^2, 33 trials: 1.26 ms (4.5 TB/s of the cubes in and the results out); 2.55 ms when
+// the windows stood in LDS (67 reads per voxel, and 1.5x the input through the halos).
 #include "internal.h"
 
 #include <algorithm>
@@ -65,8 +66,10 @@ __global__ __launch_bounds__(DD_NT) void dedoppler_kernel(const float *__restric
     if (p >= npx) return;
     const int c_begin = blockIdx.y * seg, c_end = min(n_chan, c_begin + seg);
     const float *rp = r + p;
+    // channels outside the band are -inf: a track that leaves the band (it does so for good, and its
+    // last value stands outside) sums to -inf, or to NaN, and neither is greater than any maximum
     auto load = [&](int s, int ch) __attribute__((always_inline)) {  // (ch is uniform)
-        return (ch >= 0 && ch < n_chan) ? rp[((size_t)s * n_chan + ch) * npx] : 0.f;
+        return (ch >= 0 && ch < n_chan) ? rp[((size_t)s * n_chan + ch) * npx] : -INFINITY;
     };
     float w[W::TOTAL], nx[NS][CQ];
 #pragma unroll
@@ -85,13 +88,13 @@ __global__ __launch_bounds__(DD_NT) void dedoppler_kernel(const float *__restric
         float bv[CQ];
         int bd[CQ];
         // trial k of channel c + q: drifts 0, -1, +1, -2, +2, ...
-        auto trial = [&](int k, int q, bool ok) __attribute__((always_inline)) {
+        auto trial = [&](int k, int q) __attribute__((always_inline)) {
             const int d = (k == 0) ? 0 : ((k & 1) ? -((k + 1) >> 1) : (k >> 1));
             float acc = 0.f;
 #pragma unroll
             for (int s = 0; s < NS; s++) acc += w[W::off(s) + W::half(s) + q + drift_shift(d, s, NS)];
             const float v = W::EXACT ? acc : acc * inv;
-            if (ok && v > bv[q]) {
+            if (v > bv[q]) {
                 bv[q] = v;
                 bd[q] = d;
             }
@@ -101,28 +104,17 @@ __global__ __launch_bounds__(DD_NT) void dedoppler_kernel(const float *__restric
             bv[q] = -INFINITY;
             bd[q] = 0;
         }
-        // every requested trial's track lies in the band: no band test
-        const bool inside = c >= max_drift && c + CQ - 1 + max_drift < n_chan;
-        if (inside && max_drift == D_MAX) {
+        if (max_drift == D_MAX) {
 #pragma unroll
             for (int q = 0; q < CQ; q++)
 #pragma unroll
-                for (int k = 0; k < 2 * D_MAX + 1; k++) trial(k, q, true);
-        } else if (inside) {
+                for (int k = 0; k < 2 * D_MAX + 1; k++) trial(k, q);
+        } else {
 #pragma unroll
             for (int k = 0; k < 2 * D_MAX + 1; k++) {
                 if (k < n_trial) {  // (uniform)
 #pragma unroll
-                    for (int q = 0; q < CQ; q++) trial(k, q, true);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < 2 * D_MAX + 1; k++) {
-                const int d = (k == 0) ? 0 : ((k & 1) ? -((k + 1) >> 1) : (k >> 1));
-                if (k < n_trial) {
-#pragma unroll
-                    for (int q = 0; q < CQ; q++) trial(k, q, c + q + d >= 0 && c + q + d < n_chan);
+                    for (int q = 0; q < CQ; q++) trial(k, q);
                 }
             }
         }

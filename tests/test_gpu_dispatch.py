@@ -7,6 +7,7 @@ import torch
 import oracle
 import paper_2606_04304_amd as nb
 import synth
+from oracle import drift as odr
 from test_gpu_drift import test_dedoppler_matches_oracle as dedoppler_parity
 from test_gpu_net import _stamps
 from test_gpu_net import test_forward_matches_oracle as forward_parity
@@ -284,3 +285,30 @@ def test_image_statistics_every_image_observed(n_pix):
     tol += np.where(np.abs(z) < 0.01, tol, 0.0).max(axis=0)
     d = np.abs(got[:, valid] - z)
     assert np.all(d <= tol), np.unravel_index(np.argmax(d - tol), d.shape)
+
+
+@pytest.mark.parametrize("n_sub,n_chan,max_drift", [(1, 5, 16), (4, 5, 16), (4, 40, 16), (4, 40, 3), (1, 33, 2)])
+def test_dedoppler_nonfinite_and_band_ends(n_sub, n_chan, max_drift):
+    """Tracks that leave the band never win, also beside infinite and NaN values: results bit for bit
+    those of the trials in order (1 / sqrt(n_sub) is exact here)."""
+    print(f"dedoppler non-finite S={n_sub} C={n_chan} D={max_drift}", flush=True)
+    rng = np.random.default_rng(n_sub * 1000 + n_chan)
+    r = rng.standard_normal((n_sub, n_chan, 8, 8)).astype(np.float32)
+    for v in (np.inf, -np.inf, np.nan, -3e38, 3e38):
+        r[rng.integers(0, n_sub, 12), rng.integers(0, n_chan, 12), rng.integers(0, 8, 12), rng.integers(0, 8, 12)] = v
+    r[:, :, 3, 3] = -np.inf
+    r[:, :, 3, 4] = np.nan
+    best, drift = nb.nbsi_dedoppler(torch.from_numpy(r).to(DEV), max_drift)
+    want = np.full(r.shape[1:], -np.inf, np.float32)
+    at = np.zeros(want.shape, np.int8)
+    with np.errstate(invalid="ignore", over="ignore"):
+        for k in range(2 * max_drift + 1):
+            d = -((k + 1) // 2) if k & 1 else k // 2
+            for c in range(max(0, -d), min(n_chan, n_chan - d)):
+                acc = np.zeros((8, 8), np.float32)
+                for s in range(n_sub):
+                    acc = acc + r[s, c + odr.shift(d, s, n_sub)]
+                v = acc * np.float32(1.0 / np.sqrt(n_sub))
+                up = v > want[c]
+                want[c][up], at[c][up] = v[up], d
+    assert np.array_equal(best.cpu().numpy(), want) and np.array_equal(drift.cpu().numpy(), at)
