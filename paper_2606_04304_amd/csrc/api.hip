@@ -183,6 +183,12 @@ int detect_run(nbsi_ctx *ctx, const float *img, int n_chan, int n_pix, int mode,
     void *stats = ws ? (void *)ws->stats : nullptr;
     if (!ws && (rc = nbsi_scratch(ctx, SLOT_DET_STATS, sizeof(float2) * n_chan, &stats))) return rc;
     int *counter = ws ? ws->counter : ctx->d_counter;
+    // the medians and scales of an SNR cube; without room for them they go through the cube itself
+    void *pix = nullptr;
+    if (!ws && snr && nbsi_scratch(ctx, SLOT_DET_KEYS, 2 * sizeof(float) * (size_t)n_pix * n_pix, &pix)) {
+        pix = nullptr;
+        (void)hipGetLastError();
+    }
     NBSI_TRY_HIP(ctx, launch_detect_stats(img, n_chan, n_pix, mode, (float *)stats, ctx->stream));
     int cap = ws ? ws->cap : (int)std::max<size_t>(65536, ctx->scratch_size[SLOT_DET_CAND] / sizeof(nbsi_cand));
     int count = 0;
@@ -192,7 +198,7 @@ int detect_run(nbsi_ctx *ctx, const float *img, int n_chan, int n_pix, int mode,
         if (!ws && (rc = nbsi_scratch(ctx, SLOT_DET_CAND, sizeof(nbsi_cand) * (size_t)cap, &cand))) return rc;
         NBSI_TRY_HIP(ctx, hipMemsetAsync(counter, 0, sizeof(int), ctx->stream));
         NBSI_TRY_HIP(ctx, launch_detect_scan(img, n_chan, n_pix, mode, (const float *)stats, thresh, snr,
-                                             (nbsi_cand *)cand, cap, counter, ctx->stream, ctx->d_flags));
+                                             (float *)pix, (nbsi_cand *)cand, cap, counter, ctx->stream, ctx->d_flags));
         // the usual few candidates are sorted before the count comes back: one wait per call
         NBSI_TRY_HIP(ctx, launch_detect_sort_small_dev((const nbsi_cand *)cand, counter, cap, n_chan, n_pix, out,
                                                        max_out, ctx->stream));

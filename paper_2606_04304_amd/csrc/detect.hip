@@ -720,22 +720,23 @@ __global__ __launch_bounds__(64 * REG_PX, 4) void detect_pixel_reg_kernel(const 
     }
 }
 
-// The SNR cube from the medians and scales of detect_pixel_reg_kernel, which stand in the cube's
-// first two channel planes: channels c0 .. n_chan - 1, a thread takes 4 adjacent pixels of SNR_CPB
-// channels (all loads in flight) with 16-byte accesses.  Bound by HBM (8 bytes per voxel).  The
-// pixel kernel cannot write the cube well itself: it holds 4 pixels x all channels, and 16-byte
-// pieces of 128-byte lines leave its eight line-sharing workgroups at different times (4,096 x
-// 256^2, whole call: 3.25 ms with 4-byte stores from the lanes, 1.57 ms with 16-byte ones through
-// the tile, 1.22 ms with the two kernels, of which this one takes 0.36).
+// The SNR cube from the medians and scales of detect_pixel_reg_kernel (two planes of n_pix^2; without
+// scratch they stand in the cube's own first two planes): channels c0 .. n_chan - 1, a thread takes 4
+// adjacent pixels of SNR_CPB channels (all loads in flight) with 16-byte accesses.  Bound by HBM (8
+// bytes per voxel).  The pixel kernel cannot write the cube well itself: it holds 4 pixels x all
+// channels, and 16-byte pieces of 128-byte lines leave its eight line-sharing workgroups at different
+// times (4,096 x 256^2, whole call: 3.25 ms with 4-byte stores from the lanes, 1.57 ms with 16-byte
+// ones through the tile, 1.22 ms with the two kernels, of which this one takes 0.36).
 constexpr int SNR_CPB = 8;
 __global__ __launch_bounds__(256) void snr_cube_kernel(const float *__restrict__ img, int n_chan, int n_pix, int mode,
-                                                       const float2 *__restrict__ stats, int c0, float *snr) {
+                                                       const float2 *__restrict__ stats, const float *pix_stats, int c0,
+                                                       float *snr) {
     const size_t npix2 = (size_t)n_pix * n_pix;
     const size_t p = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (p >= npix2) return;
     const int cb = c0 + blockIdx.y * SNR_CPB;
-    const float4 med = *reinterpret_cast<const float4 *>(snr + p);
-    const float4 inv = *reinterpret_cast<const float4 *>(snr + npix2 + p);
+    const float4 med = *reinterpret_cast<const float4 *>(pix_stats + p);
+    const float4 inv = *reinterpret_cast<const float4 *>(pix_stats + npix2 + p);
     float4 x[SNR_CPB];
 #pragma unroll
     for (int q = 0; q < SNR_CPB; q++)
@@ -1105,7 +1106,7 @@ hipError_t launch_detect_stats(const float *img, int n_chan, int n_pix, int mode
 }
 
 hipError_t launch_detect_scan(const float *img, int n_chan, int n_pix, int mode, const float *stats,
-                              float thresh, float *snr, nbsi_cand *cand, int cap, int *counter,
+                              float thresh, float *snr, float *pix_stats, nbsi_cand *cand, int cap, int *counter,
                               hipStream_t st, unsigned *flags) {
     const float2 *s2 = reinterpret_cast<const float2 *>(stats);
     // (an SNR cube that overlaps the images takes the kernel that has read a pixel's spectrum
@@ -1116,20 +1117,22 @@ hipError_t launch_detect_scan(const float *img, int n_chan, int n_pix, int mode,
     if (n_chan <= 64 * 64 && !overlap) {
         // the spectrum's registers are sized to it: every selection pass visits all NR of them
         const int n_blocks = n_pix * (n_pix / REG_PX);
+        float *ps = !snr ? nullptr : pix_stats ? pix_stats : snr;
 #define NBSI_REG(NR)                                                                                                 \
     hipLaunchKernelGGL(detect_pixel_reg_kernel<NR>, dim3(n_blocks), dim3(64 * REG_PX), 0, st, img, n_chan, n_pix,    \
-                       mode, s2, thresh, snr, cand, cap, counter, flags)
+                       mode, s2, thresh, ps, cand, cap, counter, flags)
         if (n_chan <= 64 * 16) NBSI_REG(16);
         else if (n_chan <= 64 * 32) NBSI_REG(32);
         else NBSI_REG(64);
 #undef NBSI_REG
         hipError_t e = hipGetLastError();
         if (e != hipSuccess || !snr) return e;
-        // channels 2 and up, then the two planes that held the statistics
+        // all channels at once, or channels 2 and up and then the two planes that held the statistics
         const unsigned nx = (unsigned)((npix2 / 4 + 255) / 256);
-        hipLaunchKernelGGL(snr_cube_kernel, dim3(nx, (unsigned)((n_chan - 2 + SNR_CPB - 1) / SNR_CPB)), dim3(256), 0,
-                           st, img, n_chan, n_pix, mode, s2, 2, snr);
-        hipLaunchKernelGGL(snr_cube_kernel, dim3(nx, 1), dim3(256), 0, st, img, 2, n_pix, mode, s2, 0, snr);
+        const int c0 = ps == snr ? 2 : 0;
+        hipLaunchKernelGGL(snr_cube_kernel, dim3(nx, (unsigned)((n_chan - c0 + SNR_CPB - 1) / SNR_CPB)), dim3(256), 0,
+                           st, img, n_chan, n_pix, mode, s2, ps, c0, snr);
+        if (c0) hipLaunchKernelGGL(snr_cube_kernel, dim3(nx, 1), dim3(256), 0, st, img, 2, n_pix, mode, s2, ps, 0, snr);
         return hipGetLastError();
     }
     const int ppw = detect_ppw(n_chan);

@@ -13,7 +13,8 @@
 // input value is read once per segment (plus its ends) and the 2D + 1 trials run from registers:
 // no LDS, no barriers.  Channels outside the band stand in the windows as -inf, so that tracks which
 // leave the band need no test: with a test per trial, the segments at the band's ends set the time
-// of every small search (2 x 400 x 48^2, full range: 25.0 us a call; 21.5 with windows in LDS, 13.9 without the tests).
+// of every small search (2 x 400 x 48^2, full range: 25.0 us a call; 21.5 with windows in LDS, 13.9
+// without the tests).
 // Bound by vector instructions (per voxel 33 x (compare, two selects; a multiply where 1 / sqrt(n_sub)
 // is not exact) and ~70 additions, partial sums shared by several trials being formed once).
 // 4 x 4,096 x 256^2, 33 trials: 1.26 ms (4.5 TB/s of the cubes in and the results out); 2.55 ms when

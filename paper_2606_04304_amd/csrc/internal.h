@@ -32,7 +32,7 @@ enum ScratchSlot {
     SLOT_CHAN_STAGE_F = 1,  // channelizer staging, float32
     SLOT_IMG_INTER = 2,     // imager: row-transformed grid
     SLOT_DET_CAND = 3,      // detector: unsorted candidates
-    SLOT_DET_KEYS = 4,      // detector: sort keys
+    SLOT_DET_KEYS = 4,      // detector: per-pixel medians and scales, later sort keys
     SLOT_DET_STATS = 5,     // detector: per-channel / per-pixel statistics
     SLOT_IMG_BL = 6,        // imager: per-channel baseline values
     SLOT_CORR_PAD = 7,      // correlator: spectra repacked to a 16-byte row stride
@@ -228,8 +228,9 @@ hipError_t launch_image_grid_stokes(const nbsi_image_plan *p, const float2 *cvis
 int nbsi_aux_stream(nbsi_ctx *ctx);  // creates the auxiliary stream and its events on first use
 hipError_t launch_detect_stats(const float *img, int n_chan, int n_pix, int mode, float *stats,
                                hipStream_t st);
+// pix_stats: 2 n_pix^2 floats for the SNR cube's medians and scales, or null
 hipError_t launch_detect_scan(const float *img, int n_chan, int n_pix, int mode,
-                              const float *stats, float thresh, float *snr, nbsi_cand *cand,
+                              const float *stats, float thresh, float *snr, float *pix_stats, nbsi_cand *cand,
                               int cap, int *counter, hipStream_t st, unsigned *flags = nullptr);
 // Sorts the candidates on the device when their count (read there) is at most
 // detect_sort_small_max() and at most cap; larger counts are left to launch_detect_sort.

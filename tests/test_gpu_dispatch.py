@@ -312,3 +312,24 @@ def test_dedoppler_nonfinite_and_band_ends(n_sub, n_chan, max_drift):
                 up = v > want[c]
                 want[c][up], at[c][up] = v[up], d
     assert np.array_equal(best.cpu().numpy(), want) and np.array_equal(drift.cpu().numpy(), at)
+
+
+@pytest.mark.parametrize("mode", [nb.NBSI_DETECT_PER_PIXEL, nb.NBSI_DETECT_PER_IMAGE])
+@pytest.mark.parametrize("n_chan,n_pix", [(3, 8), (10, 16), (11, 40), (2500, 32)])
+def test_detect_snr_cube_with_and_without_scratch(n_chan, n_pix, mode):
+    """The SNR cube from medians and scales in scratch (nbsi_detect) and in its own first planes
+    (nbsi_detect_noalloc): the same values, also after more candidates than the scratch held."""
+    print(f"detect SNR cube n_chan={n_chan} n_pix={n_pix} mode={mode}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n_chan)
+    cube = torch.randn((n_chan, n_pix, n_pix), generator=g, device=DEV)
+    cube[n_chan // 2, n_pix // 2, n_pix // 2] += 40.0
+    buf = torch.full_like(cube, float("nan"))
+    rec, _, n = nb.nbsi_detect_noalloc(cube, mode=mode, snr=buf)
+    rec2, snr, n2 = nb.nbsi_detect(cube, mode=mode, want_snr=True)
+    assert n == n2 and np.array_equal(rec, rec2) and torch.equal(buf, snr)
+    if n_chan == 2500:  # every local maximum above zero: a second pass with a longer list
+        rec3, snr3, n3 = nb.nbsi_detect(cube, mode=mode, thresh=0.0, want_snr=True)
+        assert n3 > 1 << 18 and len(rec3) == n3 and torch.equal(snr3, snr)
+        rec4, snr4, _ = nb.nbsi_detect(cube, mode=mode, want_snr=True)
+        assert np.array_equal(rec4, rec) and torch.equal(snr4, snr)
