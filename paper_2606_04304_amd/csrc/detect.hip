@@ -134,7 +134,6 @@ __device__ __forceinline__ float block_max_f(float v, float *red) {
 // LDS of one block selection
 struct SelLds {
     unsigned hist[4][256];  // four copies (by wave % 4) against atomic contention
-    int cnt[256];           // bin totals
     float pool[SEL_POOL];
     int ired[SEL_NW];
     float fred[SEL_NW];
@@ -654,7 +653,7 @@ __global__ __launch_bounds__(64 * REG_PX, 4) void detect_pixel_reg_kernel(const 
         for (int q = 0; q < CH / 64; q++) v[(CH / 64) * k + q] = tile[lane + 64 * q][wave];
     }
     const int x = gx0 + wave, y = gy;
-    // (n_pix is a multiple of REG_PX: every wave has a pixel, and all of them reach the barriers)
+    // (n_pix is a multiple of REG_PX: every wave has a pixel)
     // a spectrum holding a non-finite value is not searched (wave-uniform: one pixel per wave)
     const bool finite = ((s_bad >> wave) & 1u) == 0u;
     const bool in_hor = in_horizon(x, y, n_pix);
