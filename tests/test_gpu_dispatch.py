@@ -1,5 +1,7 @@
 """Edges of the size-dependent dispatches: shapes on both sides of every rule that picks a kernel
 or a register / tile count, against the oracle or against the general form."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -8,6 +10,7 @@ import oracle
 import paper_2606_04304_amd as nb
 import synth
 from oracle import drift as odr
+from oracle import search as osr
 from test_gpu_drift import test_dedoppler_matches_oracle as dedoppler_parity
 from test_gpu_net import _stamps
 from test_gpu_net import test_forward_matches_oracle as forward_parity
@@ -333,3 +336,39 @@ def test_detect_snr_cube_with_and_without_scratch(n_chan, n_pix, mode):
         assert n3 > 1 << 18 and len(rec3) == n3 and torch.equal(snr3, snr)
         rec4, snr4, _ = nb.nbsi_detect(cube, mode=mode, want_snr=True)
         assert np.array_equal(rec4, rec) and torch.equal(snr4, snr)
+
+
+@pytest.mark.parametrize("n_chan", [1500, 2100])
+def test_search_default_bank_marches(n_chan):
+    """Workgroups that march over three and five 128-channel blocks, the last ones ragged, and passes of
+    more than one tile per wave (256 x 256 pixels): sampled spectra against the oracle, and the whole
+    cubes bit for bit those of the general kernel, which takes any other list of widths, wherever the
+    width added to the list does not win; with the width cube, without it, and without either cube."""
+    print(f"search default bank marches n_chan={n_chan}", flush=True)
+    n_pix = 256
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n_chan)
+    x = torch.randn((n_chan, n_pix, n_pix), generator=g, device=DEV)
+    rng = np.random.default_rng(n_chan)
+    for c0, w in ((100, 40), (120, 20), (250, 12), (383, 3), (500, 100), (n_chan - 30, 30), (0, 5), (1279, 2)):
+        px, py = rng.integers(70, 180, 2)
+        x[c0:c0 + w, py, px] += 20.0 / w ** 0.5
+    x[700, 128, 130], x[300, 127, 131], x[n_chan - 1, 126, 132], x[2, 125, 133] = np.inf, np.nan, -np.inf, np.inf
+    rec, thr, k, S, W = nb.nbsi_search(x, want_cubes=True)
+    rec2, thr2, k2, _, _ = nb.nbsi_search(x)
+    assert (thr, k) == (thr2, k2) and np.array_equal(rec, rec2) and len(rec) >= 8
+    only = torch.empty_like(S)  # best SNRs without the widths, through the C entry point
+    ctx = nb.nbsi_create(0)
+    ctx._sync_stream()
+    n_out, out = ctypes.c_int(), torch.empty((4096, 5), dtype=torch.int32, device=DEV)
+    assert nb.lib().nbsi_search_corr(ctx._h, x.data_ptr(), n_chan, n_pix, None, 0, None, 0, 0.01, only.data_ptr(), None,
+                                     out.data_ptr(), 4096, ctypes.byref(n_out), None, None) == 0
+    assert n_out.value == len(rec) and torch.equal(only, S)
+    _, _, _, Sg, Wg = nb.nbsi_search(x, widths=list(osr.WIDTHS) + [127], want_cubes=True)
+    same = Wg != 127
+    assert torch.equal(S[same], Sg[same]) and torch.equal(W[same], Wg[same]) and bool((S <= Sg).all())
+    assert float(same.float().mean()) > 0.9
+    pix = rng.integers(0, n_pix * n_pix, 24)
+    pix = torch.from_numpy(pix[(pix // n_pix < 120) | (pix // n_pix > 132)]).to(DEV)  # (finite spectra)
+    spectra = x.view(n_chan, -1)[:, pix].cpu().numpy()
+    _check_bank(spectra, S.view(n_chan, -1)[:, pix], W.view(n_chan, -1)[:, pix])
