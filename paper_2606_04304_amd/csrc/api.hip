@@ -183,9 +183,13 @@ int detect_run(nbsi_ctx *ctx, const float *img, int n_chan, int n_pix, int mode,
     void *stats = ws ? (void *)ws->stats : nullptr;
     if (!ws && (rc = nbsi_scratch(ctx, SLOT_DET_STATS, sizeof(float2) * n_chan, &stats))) return rc;
     int *counter = ws ? ws->counter : ctx->d_counter;
-    // the medians and scales of an SNR cube; without room for them they go through the cube itself
+    // the medians and scales of an SNR cube stand where the sort keys come later; without room for
+    // them (fixed workspace: beyond 256 x 256 pixels) they go through the cube itself
     void *pix = nullptr;
-    if (!ws && snr && nbsi_scratch(ctx, SLOT_DET_KEYS, 2 * sizeof(float) * (size_t)n_pix * n_pix, &pix)) {
+    const size_t pix_bytes = 2 * sizeof(float) * (size_t)n_pix * n_pix;
+    if (snr && ws) {
+        if (pix_bytes <= sizeof(unsigned long long) * (size_t)ws->cap) pix = ws->keys;
+    } else if (snr && nbsi_scratch(ctx, SLOT_DET_KEYS, pix_bytes, &pix)) {
         pix = nullptr;
         (void)hipGetLastError();
     }

@@ -720,13 +720,14 @@ __global__ __launch_bounds__(64 * REG_PX, 4) void detect_pixel_reg_kernel(const 
 }
 
 // The SNR cube from the medians and scales of detect_pixel_reg_kernel (two planes of n_pix^2; without
-// scratch they stand in the cube's own first two planes): channels c0 .. n_chan - 1, a thread takes 4
+// room for them they stand in the cube's own first two planes): channels c0 .. n_chan - 1, a thread takes 4
 // adjacent pixels of SNR_CPB channels (all loads in flight) with 16-byte accesses.  Bound by HBM (8
 // bytes per voxel).  The pixel kernel cannot write the cube well itself: it holds 4 pixels x all
 // channels, and 16-byte pieces of 128-byte lines leave its eight line-sharing workgroups at different
 // times (4,096 x 256^2, whole call: 3.25 ms with 4-byte stores from the lanes, 1.57 ms with 16-byte
-// ones through the tile, 1.22 ms with the two kernels, of which this one takes 0.36).
-constexpr int SNR_CPB = 8;
+// ones through the tile, 1.22 ms with the two kernels, of which this one takes 0.35; 0.36 with eight
+// channels a thread).
+constexpr int SNR_CPB = 4;
 __global__ __launch_bounds__(256) void snr_cube_kernel(const float *__restrict__ img, int n_chan, int n_pix, int mode,
                                                        const float2 *__restrict__ stats, const float *pix_stats, int c0,
                                                        float *snr) {

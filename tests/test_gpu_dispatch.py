@@ -318,10 +318,11 @@ def test_dedoppler_nonfinite_and_band_ends(n_sub, n_chan, max_drift):
 
 
 @pytest.mark.parametrize("mode", [nb.NBSI_DETECT_PER_PIXEL, nb.NBSI_DETECT_PER_IMAGE])
-@pytest.mark.parametrize("n_chan,n_pix", [(3, 8), (10, 16), (11, 40), (2500, 32)])
+@pytest.mark.parametrize("n_chan,n_pix", [(3, 8), (10, 16), (11, 256), (2500, 32), (3, 264), (7, 512)])
 def test_detect_snr_cube_with_and_without_scratch(n_chan, n_pix, mode):
-    """The SNR cube from medians and scales in scratch (nbsi_detect) and in its own first planes
-    (nbsi_detect_noalloc): the same values, also after more candidates than the scratch held."""
+    """The SNR cube from medians and scales in scratch (nbsi_detect), in the fixed workspace or, beyond
+    256 x 256 pixels, in its own first planes (nbsi_detect_noalloc): the same values, also after more
+    candidates than the scratch held."""
     print(f"detect SNR cube n_chan={n_chan} n_pix={n_pix} mode={mode}", flush=True)
     g = torch.Generator(device="cuda")
     g.manual_seed(n_chan)
