@@ -514,8 +514,11 @@ def search_leg(args, nb, torch, ctx, dev, C, n_pix):
     ms = (time.perf_counter() - t0) * 1e3 / reps
     rec, thr, kprov = res[0], res[1], res[2]
     vox = C * n_pix * n_pix
-    # bank: the SNR cube in, best SNR (4 B) and width (1 B) out; accept: the best SNR read again
-    algo = vox * 4 + vox * 5 + vox * 4
+    # the SNR cube in, the best SNRs (scratch, read again by the later passes where they matter) out;
+    # runs of 64 pixels wholly outside the horizon are skipped
+    yy, xx = np.mgrid[:n_pix, :n_pix] - n_pix // 2
+    searched = ((xx * xx + yy * yy) < (n_pix // 2) ** 2).reshape(-1, 64).any(axis=1).sum() * 64
+    algo = C * int(searched) * 8
     log(f"[bench] stage I search: {ms:.3f} ms, k* {kprov}, S* {thr:.3f}, {len(rec)} candidates")
     del snr
     torch.cuda.empty_cache()
