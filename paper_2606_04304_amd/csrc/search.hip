@@ -21,7 +21,7 @@
 //    p_(k) <= k q / m; only a bin where that is undecided by its edges is gathered exactly
 //    (search_gather_kernel) and sorted on the host.
 //  * search_accept_kernel lists the accepted voxels, search_width_kernel finds their widths when no
-//    width cube was made, search_nms_kernel (a wave each) keeps those no neighbour suppresses, and
+//    width cube was made, search_nms_kernel keeps those no neighbour suppresses, and
 //    search_refine_kernel (a workgroup per survivor) re-evaluates them, its medians from an exact
 //    rank count over at most 512 flank values.
 #include "internal.h"
@@ -229,10 +229,12 @@ __global__ __launch_bounds__(256) void search_bank_kernel(const float *__restric
 // read once.  A wave takes its 32 channels in two groups of 16: the 116 prefix sums that all 26
 // windows of 16 channels touch (scan + offset of their segment, the general kernel's own sum) are
 // read into registers once, and the windows are differences of registers.
-// Bound by vector instructions: per voxel and width a difference, a product and half of a
-// three-way maximum; the width of the maximum (a compare and a select more) is kept only when the
-// caller wants the width cube.  4,096 x 256^2: 0.90 ms (1.35 with the widths), against 2.77 ms for
-// the general kernel, which reads every row twice from memory and 52 prefix sums per voxel from LDS.
+// Bound by vector instructions first (per voxel and width a difference, a product and half of a
+// three-way maximum; 94 in all, which fill 70% of the issue slots), then by the waits of two
+// workgroups per CU (32% of the waves' life); the width of the maximum (a compare and a select more)
+// is kept only when the caller wants the width cube.  4,096 x 256^2: 0.90 ms (1.35 with the widths),
+// against 2.77 ms for the general kernel, which reads every row twice from memory and 52 prefix sums
+// per voxel from LDS.
 constexpr int STD_N = 26;
 __host__ __device__ constexpr int std_width(int k) {
     constexpr int w[STD_N] = {1,  2,  3,  4,  5,  6,  7,  8,  9,  10, 12, 16, 20,
